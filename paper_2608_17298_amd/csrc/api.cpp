@@ -65,7 +65,7 @@ Layout make_layout(int64_t n, int K, int64_t pair_cap, int mode, int tile, int64
   L.partials = take(size_t((nn + kBoundsBlock - 1) / kBoundsBlock) * 16);
   L.status = take(4);
   L.hl_off = take(size_t(nt + 1) * 8);  // first hit_list row of each tile
-  L.tile_visit = take(size_t(nt) * 4);  // the forward's visited prefix of each tile's list
+  L.tile_visit = take(size_t(nt) * (size_t(tile) * tile / 64) * 4);  // the forward's visited prefixes of each tile's list
   const size_t AS = size_t(acc_stride(K));
   const bool rows = mode == GART_BACKWARD_GATHER || mode == GART_BACKWARD_GATHER_WAVE || mode == GART_BACKWARD_HYBRID;
   L.acc = take(rows ? 4 : size_t(nn) * AS * 4);

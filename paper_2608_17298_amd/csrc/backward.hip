@@ -290,10 +290,13 @@ __global__ __launch_bounds__(TILE* TILE, 2) void gather_kernel(BackwardArgs A) {
   }
   __syncthreads();
 
-  // Composited hits lie in the first tile_visit[tile] positions of the tile's
-  // list (the forward records one past the largest position it composited).
+  // Composited hits lie in the first `visit` positions of the tile's list (the
+  // forward records one past the largest position each of its waves composited).
   const int64_t beg = A.tile_range[tile], end = A.tile_range[tile + 1];
-  const int64_t vend = min(end, beg + int64_t(A.tile_visit[tile]));
+  uint32_t visit = A.tile_visit[int64_t(tile) * G];
+#pragma unroll
+  for (int w = 1; w < G; ++w) visit = max(visit, A.tile_visit[int64_t(tile) * G + w]);
+  const int64_t vend = min(end, beg + int64_t(visit));
 
   uint32_t n_pairs = 0, n_hits = 0, n_atom = 0, n_active = 0, n_wave = 0;
   for (int64_t c0 = beg; c0 < vend; c0 += kPairs) {

@@ -46,16 +46,19 @@ __host__ __device__ constexpr int acc_stride(int K) {
   return acc_width(K) <= 16 ? 16 : (acc_width(K) + 31) / 32 * 32;
 }
 
-// Unit world-space ray direction through the centre of pixel (px, py).
-__device__ __forceinline__ void pixel_ray(const CamParams& c, int px, int py, double d[3]) {
+// Unit world-space ray direction through the centre of pixel (px, py): the
+// vector R^T u of the camera ray u = (a, b, 1), normalised.
+__device__ __forceinline__ void pixel_ray(const CamParams& c, int px, int py, double d[3], double* w2 = nullptr) {
   const double a = (double(px) + 0.5 - c.cx) / c.fx;
   const double b = (double(py) + 0.5 - c.cy) / c.fy;
   double v[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) v[k] = fma(c.Rt[3 * k], a, fma(c.Rt[3 * k + 1], b, c.Rt[3 * k + 2]));
-  const double inv = 1.0 / sqrt(fma(v[0], v[0], fma(v[1], v[1], v[2] * v[2])));
+  const double vv = fma(v[0], v[0], fma(v[1], v[1], v[2] * v[2]));
+  const double inv = 1.0 / sqrt(vv);
 #pragma unroll
   for (int k = 0; k < 3; ++k) d[k] = v[k] * inv;
+  if (w2) *w2 = vv;
 }
 
 // Unit camera-space direction c through the centre of tile (tx, ty) (its
@@ -87,6 +90,31 @@ __device__ __forceinline__ double key_scale(const CamParams& cam, const double c
   return sqrt(w2) / fma(c[0], a, fma(c[1], b, c[2])) * (1.0 - 0x1p-40);
 }
 
+// pixel_ray, and key_scale of the ray in fp32: every step is within a few ulp
+// (the terms of c . u do not cancel: c and u are directions of one tile), and
+// the result is lowered by 2^-17, so that it stays below key_scale.
+__device__ __forceinline__ float pixel_ray_scale(const CamParams& cam, int px, int py, int tx, int ty, int ts,
+                                                 double d[3]) {
+  double w2;
+  pixel_ray(cam, px, py, d, &w2);
+  const float ifx = float(cam.ifx), ify = float(cam.ify);
+  const float a = float(double(px) + 0.5 - cam.cx) * ifx, b = float(double(py) + 0.5 - cam.cy) * ify;
+  const float ca = float(double(tx * ts) + 0.5 * ts - cam.cx) * ifx, cb = float(double(ty * ts) + 0.5 * ts - cam.cy) * ify;
+  const float cu = fmaf(ca, a, fmaf(cb, b, 1.0f));
+  return sqrtf(float(w2) * fmaf(ca, ca, fmaf(cb, cb, 1.0f))) / cu * (1.0f - 0x1p-17f);
+}
+
+// num / den for den in the normal range: the hardware reciprocal refined by
+// two Newton steps, the quotient by its residual (error below 0.51 ulp; the
+// division's scaling for subnormal and overflowing operands is left out).
+__device__ __forceinline__ double quotient(double num, double den) {
+  double r = __builtin_amdgcn_rcp(den);
+  r = fma(r, fma(-den, r, 1.0), r);
+  r = fma(r, fma(-den, r, 1.0), r);
+  const double q = num * r;
+  return fma(fma(-den, q, num), r, q);
+}
+
 // Max-response point of a Gaussian on the ray o + tau d (Eq. 4-5) in the
 // Gaussian's normalised frame: d_g = W d, tau = -<o_g, d_g> / <d_g, d_g>,
 // x_g = o_g + tau d_g, D2 = |x_g|^2.  Returns the hit decision tau > 0 and
@@ -98,7 +126,7 @@ __device__ __forceinline__ bool ray_hit(const double W[9], const double og[3], d
   for (int k = 0; k < 3; ++k) dg[k] = fma(W[3 * k], d[0], fma(W[3 * k + 1], d[1], W[3 * k + 2] * d[2]));
   const double num = fma(og[0], dg[0], fma(og[1], dg[1], og[2] * dg[2]));
   const double den = fma(dg[0], dg[0], fma(dg[1], dg[1], dg[2] * dg[2]));
-  const double tau = -num / den;
+  const double tau = -quotient(num, den);
 #pragma unroll
   for (int k = 0; k < 3; ++k) xg[k] = fma(tau, dg[k], og[k]);
   const double D2 = fma(xg[0], xg[0], fma(xg[1], xg[1], xg[2] * xg[2]));

@@ -1,408 +1,676 @@
 // Forward software trace (Sec. 3.2-3.3, Eq. 3-8) writing the (L, T)
 // intermediate buffer in primitive-major order (Sec. 4.3, Eq. 16).
 //
-// One workgroup per tile, one lane per pixel.  The tile's Gaussian list is
+// One wave per 8x8 pixels, one lane per pixel.  The tile's Gaussian list is
 // ordered by a lower bound on the depth at which each Gaussian can be hit by
 // a pixel ray of the tile, so a lane can stream it front to back with a small
-// sorted buffer of pending hits: a buffered hit is final -- and is composited
+// sorted pool of pending hits: a pending hit is final -- and is composited
 // -- as soon as its depth is below the bound of the next Gaussian in the list.
-// The result is exactly the (tau, index) order.  The buffer is a ring of KB
-// entries per lane in LDS, laid out [slot][lane], so the lanes of a wave
-// touch consecutive words whatever slot each is at (no bank conflicts); a new
-// hit is inserted from the tail, which with tight bounds is nearly always an
-// append.  If a ring overflows, its largest hits are dropped and the lane
-// later rescans the list from the first Gaussian it dropped, skipping hits
-// already composited; compositing stops once the transmittance falls below
-// t_min.
+// The result is exactly the (tau, index) order.
+//
+// What bounds it: the instructions of a wave's chain (33 steps of four
+// candidates and 60 compositing steps per tile at 1M Gaussians, half of them
+// fp64) at the two waves per SIMD that the pools' LDS leaves, and about a
+// sixth of the time the waits for rows.  A branch costs a lone wave some 45
+// cycles, ten times an fp64 operation, and a load issued in the chain its
+// whole latency.  So:
+//  - The list is taken in chunks of 64 positions, one per lane: rectangles
+//    become 64-bit masks of the wave's pixels, and the candidates that no
+//    working lane can hit are dropped by a permutation of the lanes.
+//  - The rest come in groups of four, whose rows (geometry, SH) are loaded a
+//    group ahead and staged in LDS.  The four ray tests, exponentials and pool
+//    insertions are straight-line code for all lanes.
+//  - Colours are evaluated where a Gaussian is the same for the whole wave, on
+//    the matrix cores (4x4x1 fp32: one block per four pixels, the SH block of
+//    the four candidates broadcast), instead of 3K scattered loads and 3K
+//    FMAs per composited hit.
+//  - The pool is a sorted list of 32-bit keys in registers (the depth as a
+//    float, its low bits replaced by the hit's payload slot) and the payload
+//    (alpha, colour, list position) in LDS; a chain of medians inserts a key.
+//    Hits whose keys tie are ordered on their exact depths, recomputed.
+// Against one candidate at a time, branches around each part and colours at
+// the compositing (ms): 1M Gaussians 1.47 -> 0.93, 4M 2.52 -> 1.56, 100k 0.57
+// -> 0.36, 150k large 9.9 -> 5.64, 250k on 16x16 tiles 1.91 -> 0.54, 4k 0.41
+// -> 0.12.
+// If a pool overflows, its largest hits are dropped and the lane later
+// rescans the list from the first Gaussian it dropped, skipping hits already
+// composited; compositing stops once the transmittance falls below t_min.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
+#include <utility>
 
 #include "ops.h"
 
 namespace gart {
 namespace {
 
-#ifndef GART_FWD_FLUSH
-#define GART_FWD_FLUSH 8
-#endif
-#ifndef GART_FWD_BATCH
-#define GART_FWD_BATCH 16
-#endif
-
-constexpr int kRow = 20;  // doubles per staged Gaussian in LDS
-// row: [0..8] W, [9..11] o_g, [12] D2c, [13] sigma, [14] depth key,
-// [15] O_prim (int64 bits), [16..17] rect (4 x int32), [18] index (uint32)
+constexpr int kGroup = 4;     // candidates per step (sixteen lanes load each one's row)
+constexpr int kChunk = 64;    // list positions looked at together, one per lane
+constexpr int kWindow = 128;  // list positions whose (L,T) addressing is kept in LDS
+constexpr int kPoolSpare = 4;  // free entries below which a lane's final hits are composited
 
 // Each rescan composites at least one hit per rescanning lane, so the pass
 // count is bounded by the hits of a tile; this cap only guards against a
 // defect turning into a hang, and is reported in the frame status if reached.
 constexpr int kMaxPasses = 1 << 20;
 
-// Minimum 64-thread workgroups per CU asked of the register allocator (default: none).
-#ifdef GART_FWD_MINBLOCKS
-#define GART_FWD_LAUNCH_BOUNDS(n) __launch_bounds__(n) __attribute__((amdgpu_waves_per_eu(GART_FWD_MINBLOCKS / 4)))
-#else
-#define GART_FWD_LAUNCH_BOUNDS(n) __launch_bounds__(n)
-#endif
+using f32x4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
+
+// Orders LDS accesses of the (single-wave) block: LDS executes a wave's
+// accesses in issue order, so only the compiler has to keep them.
+__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, int lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane(int(uint32_t(v)), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(int(uint32_t(v >> 32)), lane);
+  return uint64_t(hi) << 32 | lo;
+}
+
+__device__ __forceinline__ bool lane_bit(uint64_t wave_mask) { return __builtin_amdgcn_inverse_ballot_w64(wave_mask); }
+
+// d[r] (r = 0..3) += sum_k a_k[r] * Y[k] per lane, a_k[r] = a of lane 4k + r:
+// the SH sums of four Gaussians (one channel) at the lane's pixel.
+template <int... Ks>
+__device__ __forceinline__ void sh_mfma(std::integer_sequence<int, Ks...>, float r, float g, float b, const float* Y,
+                                        f32x4& dr, f32x4& dg, f32x4& db) {
+  ((dr = __builtin_amdgcn_mfma_f32_4x4x1f32(r, Y[Ks], dr, 4, Ks, 0),
+    dg = __builtin_amdgcn_mfma_f32_4x4x1f32(g, Y[Ks], dg, 4, Ks, 0),
+    db = __builtin_amdgcn_mfma_f32_4x4x1f32(b, Y[Ks], db, 4, Ks, 0)),
+   ...);
+}
+
+// Non-negative colour -> the frame's fixed point, rounded to nearest by the
+// addition of 2^52 (the integer is the low word of the sum); values from 2^32
+// on and NaN saturate.
+__device__ __forceinline__ uint32_t color_fixed_fma(double v, double inv_step) {
+  const uint64_t u = __double_as_longlong(fma(v, inv_step, 0x1p52));
+  return uint32_t(u >> 32) == 0x43300000u ? uint32_t(u) : 0xffffffffu;
+}
+
+// 2^(j / 64) for j = 0 .. 63 is kept in LDS: exp(-D2 / 2) = 2^(n / 64) 2^(r / 64)
+// with n integer and |r| <= 1/2, the second factor by its Taylor series to the
+// fifth order (remainder below 2^-54).
+constexpr int kExpSteps = 64;
+__constant__ const double kExp2[64] = {
+    0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0, 0x1.0874518759bc8p+0,
+    0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0, 0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0,
+    0x1.172b83c7d517bp+0, 0x1.1a35beb6fcb75p+0, 0x1.1d4873168b9aap+0, 0x1.2063b88628cd6p+0,
+    0x1.2387a6e756238p+0, 0x1.26b4565e27cddp+0, 0x1.29e9df51fdee1p+0, 0x1.2d285a6e4030bp+0,
+    0x1.306fe0a31b715p+0, 0x1.33c08b26416ffp+0, 0x1.371a7373aa9cbp+0, 0x1.3a7db34e59ff7p+0,
+    0x1.3dea64c123422p+0, 0x1.4160a21f72e2ap+0, 0x1.44e086061892dp+0, 0x1.486a2b5c13cd0p+0,
+    0x1.4bfdad5362a27p+0, 0x1.4f9b2769d2ca7p+0, 0x1.5342b569d4f82p+0, 0x1.56f4736b527dap+0,
+    0x1.5ab07dd485429p+0, 0x1.5e76f15ad2148p+0, 0x1.6247eb03a5585p+0, 0x1.6623882552225p+0,
+    0x1.6a09e667f3bcdp+0, 0x1.6dfb23c651a2fp+0, 0x1.71f75e8ec5f74p+0, 0x1.75feb564267c9p+0,
+    0x1.7a11473eb0187p+0, 0x1.7e2f336cf4e62p+0, 0x1.82589994cce13p+0, 0x1.868d99b4492edp+0,
+    0x1.8ace5422aa0dbp+0, 0x1.8f1ae99157736p+0, 0x1.93737b0cdc5e5p+0, 0x1.97d829fde4e50p+0,
+    0x1.9c49182a3f090p+0, 0x1.a0c667b5de565p+0, 0x1.a5503b23e255dp+0, 0x1.a9e6b5579fdbfp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b33a2b84f15fbp+0, 0x1.b7f76f2fb5e47p+0, 0x1.bcc1e904bc1d2p+0,
+    0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0, 0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0,
+    0x1.d5818dcfba487p+0, 0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
+    0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0,
+};
+__device__ __forceinline__ double exp_neg_half(double D2, const double* table) {
+  constexpr double kC = -0x1.71547652b82fep+5;  // -64 log2(e) / 2, and what its rounding leaves
+  constexpr double kCLow = -0x1.777d0ffda0d24p-51;
+  constexpr double k1 = 0x1.62e42fefa39efp-7;  // ln 2 / 64, and its powers over i!
+  constexpr double k2 = k1 * k1 / 2, k3 = k2 * k1 / 3, k4 = k3 * k1 / 4, k5 = k4 * k1 / 5;
+  const double t = fma(D2, kC, 0x1.8p52);
+  const int n = int(uint32_t(__double_as_longlong(t)));
+  const double nd = t - 0x1.8p52;
+  const double r = fma(D2, kCLow, fma(D2, kC, -nd));
+  const double q = r * fma(r, fma(r, fma(r, fma(r, k5, k4), k3), k2), k1);
+  const uint64_t u = __double_as_longlong(table[n & (kExpSteps - 1)]);
+  const double f = __longlong_as_double(u + (uint64_t(uint32_t((n & ~(kExpSteps - 1)) << 14)) << 32));
+  return fma(f, q, f);
+}
+
+// max(x, 0); 0 for NaN.
+__device__ __forceinline__ float max_zero(float x) {
+  float r;
+  asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
+// LDS writes by the lanes of the mask (a branch around them would cost more
+// than they do).
+__device__ __forceinline__ void lds_write_masked(uint64_t mask, uint4* p4, uint4 v4, uint2* p2, uint2 v2) {
+  using u32x4 = __attribute__((__vector_size__(16))) uint32_t;
+  using u32x2 = __attribute__((__vector_size__(8))) uint32_t;
+  const uint32_t a4 = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint4*)p4));
+  const uint32_t a2 = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint2*)p2));
+  const u32x4 w4 = {v4.x, v4.y, v4.z, v4.w};
+  const u32x2 w2 = {v2.x, v2.y};
+  uint64_t exec;
+  asm volatile(
+      "s_mov_b64 %0, exec\n\t"
+      "s_mov_b64 exec, %1\n\t"
+      "ds_write_b128 %2, %3\n\t"
+      "ds_write_b64 %4, %5\n\t"
+      "s_mov_b64 exec, %0"
+      : "=&s"(exec)
+      : "s"(mask), "v"(a4), "v"(w4), "v"(a2), "v"(w2)
+      : "memory");
+}
+
+__device__ __forceinline__ f32x4 rot(f32x4 v) { return f32x4{v[1], v[2], v[3], v[0]}; }
+
+// Pixels of the wave's 8x8 block (bit 8 y + x) inside the rectangle r.
+__device__ __forceinline__ uint64_t rect_mask(int4 r, int ox, int oy) {
+  // columns and rows as 8-bit masks; a row bit becomes a byte of columns
+  const int x0 = min(max(r.x - ox, 0), 8), x1 = max(min(r.z - ox, 7), -1);
+  const int y0 = min(max(r.y - oy, 0), 8), y1 = max(min(r.w - oy, 7), -1);
+  const uint32_t col = (0xffu >> (7 - x1)) & (0xffu << x0) & 0xffu, row = (0xffu >> (7 - y1)) & (0xffu << y0) & 0xffu;
+  const uint32_t lo = ((row & 15u) * 0x204081u & 0x01010101u) * col;
+  const uint32_t hi = ((row >> 4) * 0x204081u & 0x01010101u) * col;
+  return uint64_t(hi) << 32 | lo;
+}
 
 template <int TILE, int K, int FMT, int KB>
-__global__ GART_FWD_LAUNCH_BOUNDS(TILE* TILE) void forward_kernel(ForwardArgs A) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void forward_kernel(ForwardArgs A) {
   constexpr int NT = TILE * TILE;
-  constexpr int kFlushEvery = GART_FWD_FLUSH;
-  constexpr int NB = GART_FWD_BATCH < NT ? GART_FWD_BATCH : NT;  // candidates staged per batch
+  constexpr int G = NT / 64;  // 8x8 blocks (waves) per tile
+  constexpr int SB = KB <= 8 ? 3 : 4;
+  constexpr uint32_t SM = (1u << SB) - 1u;  // payload slot bits of a pool key
+  constexpr uint32_t kEmpty = UINT_MAX;
   constexpr double kInf = __builtin_huge_val();
-  static_assert(KB >= 2 && (KB & (KB - 1)) == 0, "ring of a power-of-two size");
+  constexpr uint32_t kPosMask = 0x7fffffffu;  // list position of a payload; the top bit: found by an exact scan
+  static_assert(KB >= 2 && KB <= 16, "pool slots fit the key's low bits");
 
-  __shared__ __align__(16) double s_row[NB * kRow];
-  __shared__ float s_key[NB + 1];
-  __shared__ unsigned s_restart;
-  // pending hits of each lane: depth rounded up to a float, alpha, and
-  // (list position, Gaussian index) -- 20 bytes; the exact depth is
-  // recomputed on the rare paths that need it.  Large rings keep the list
-  // position only (16 bytes, the index is read from the list when needed):
-  // the LDS saved raises occupancy where the ring is what limits it.
-  constexpr bool kPosOnly = KB >= 16;
-  __shared__ float s_btf[KB][NT];
-  __shared__ double s_balpha[KB][NT];
-  __shared__ uint32_t s_bpos[KB][NT];
-  __shared__ uint32_t s_bid[kPosOnly ? 1 : KB][kPosOnly ? 1 : NT];
+  __shared__ __align__(16) double s_row[kGroup * 16];  // W (9), o_g (3), D2c, sigma, -, -
+  __shared__ uint4 s_win[kWindow];                     // (L,T) address (64 bits), row length, Gaussian index
+  __shared__ double s_exp[kExpSteps];
+  __shared__ uint4 s_pa[KB * 64];                      // payload: alpha (fp64), colour r, g
+  __shared__ uint2 s_pb[KB * 64];                      //          colour b, list position
 
   const int n_tiles = A.tiles_x * A.tiles_y;
-  const int tile = xcd_tile(blockIdx.x, n_tiles, A.tiles_x);
+  const int lane = threadIdx.x;
+  int slot_of_tile = blockIdx.x, grp = 0;
+  if constexpr (G > 1) {  // the waves of a tile on one XCD (blocks reach the XCDs round-robin)
+    slot_of_tile = int(blockIdx.x / (8 * G)) * 8 + int(blockIdx.x % 8);
+    grp = int(blockIdx.x / 8) % G;
+    if (slot_of_tile >= n_tiles) return;
+  }
+  const int tile = xcd_tile(slot_of_tile, n_tiles, A.tiles_x);
   const int tx = tile % A.tiles_x, ty = tile / A.tiles_x;
-  const int tid = threadIdx.x;
-  const int px = tx * TILE + tid % TILE, py = ty * TILE + tid / TILE;
+  constexpr int kBlocksX = TILE / 8;
+  const int ox = tx * TILE + 8 * (grp % kBlocksX), oy = ty * TILE + 8 * (grp / kBlocksX);
+  const int px = ox + lane % 8, py = oy + lane / 8;
+  const int q_tile = (py - ty * TILE) * TILE + (px - tx * TILE);  // pixel of the tile, row-major
   const bool valid = px < A.cam.W && py < A.cam.H;
 
+  // The tile's list keys are depths along the tile's axis; key k bounds the
+  // depth of a hit on this pixel's ray by k * kscale.
   double d[3];
-  pixel_ray(A.cam, valid ? px : 0, valid ? py : 0, d);
-  // the tile's list keys are depths along the tile's axis; key k bounds the
-  // depth of a hit on this pixel's ray by k * kscale
-  double cax[3];
-  tile_axis(A.cam, tx, ty, TILE, cax);
-  const double kscale = key_scale(A.cam, cax, valid ? px : 0, valid ? py : 0);
+  const float kscale = pixel_ray_scale(A.cam, valid ? px : 0, valid ? py : 0, tx, ty, TILE, d);
   float Y[K];  // SH basis of this pixel's ray
   sh_basis<K>(float(d[0]), float(d[1]), float(d[2]), Y);
 
-  const int64_t beg = A.tile_range[tile], end = A.tile_range[tile + 1];
+  const int64_t beg = A.tile_range[tile];
+  const int n = int(A.tile_range[tile + 1] - beg);  // below the number of Gaussians, 2^31
   const int64_t hl_beg = A.hl_off[tile];  // this tile's first hit_list row
   // its rows (>= 1 if the tile has pairs); a hit beyond them, which the
   // bound on hits per pixel excludes, would overwrite the last row and is
   // reported in the frame status after the trace
   const uint32_t hl_last = uint32_t(max<int64_t>(A.hl_off[tile + 1] - hl_beg, 1) - 1);
-  // Gaussian index of ring entry s
-  auto entry_id = [&](int s) -> uint32_t {
-    if constexpr (kPosOnly) return A.pair_prim[beg + s_bpos[s][tid]];
-    else return s_bid[s][tid];
-  };
+  uint32_t* const hl = A.hit_list + int64_t(NT) * hl_beg;
+  s_exp[lane] = kExp2[lane];
+  const uint32_t* prim = A.pair_prim + beg;
+  const float* pkey = A.pair_key + beg;
 
   double T = 1.0, L0 = 0.0, L1 = 0.0, L2 = 0.0;
-  bool done = !valid;     // terminated (or no pixel)
-  bool finished = false;  // every hit composited
-  bool stalled = false;   // must wait for a rescan
-  uint32_t n_hits = 0, n_tests = 0, n_drops = 0;
+  uint32_t n_hits = 0, n_drops = 0;
+  uint32_t n_tests = 0;  // of the wave
   uint32_t visited = 0;  // one past the largest list position composited
   double last_tau = -kInf;
   uint32_t last_id = 0;
-  double end_tau = kInf;
-  uint32_t end_id = kNoPrim;
 
-  int head = 0, cnt = 0;  // ring: entries head, head + 1, ... (mod KB), sorted by (depth, index)
-  double e_tau = kInf;    // lower bound on the depths of dropped hits (every buffered hit is smaller)
-  // The ring's head entry (depth bound, alpha, list position, index) and the
-  // tail's depth bound are kept in registers: a plain append and each
-  // compositing step then need no LDS round trip to find them.
-  float head_tf = __int_as_float(0x7f800000);  // +inf if empty
-  double head_a = 0.0;
-  uint32_t head_pos = 0, head_id = 0;
-  float tail_tf = 0.0f;                        // valid while cnt > 0
-  uint32_t jr = UINT_MAX;  // first list position holding a dropped hit
+  // Pool: keys a[0 .. cnt) ascending, the rest kEmpty; the free payload slots
+  // as a stack of 4-bit numbers.
+  using Stack = std::conditional_t<KB <= 8, uint32_t, uint64_t>;
+  uint32_t a[KB];
+#pragma unroll
+  for (int s = 0; s < KB; ++s) a[s] = kEmpty;
+  uint32_t cnt = 0;
+  Stack free_slots = Stack(0xfedcba9876543210ull);
+  uint32_t e_key = UINT_MAX;  // smallest depth key (low bits clear) of the dropped hits; every pooled key is below it
+  uint32_t jr = UINT_MAX;     // first list position holding a dropped hit
   // A rescan starts the wave at the smallest jr of its lanes; a lane skips
   // the positions before its own jr (from): every hit there was composited
   // in an earlier pass.
   uint32_t from = 0;
+  uint32_t win_lo = 0;  // list positions from here on are in s_win
 
-  // A dropped hit at list position c whose depth is at least t_lb.
-  auto drop = [&](double t_lb, uint32_t c) {
-    ++n_drops;
-    e_tau = fmin(e_tau, t_lb);
-    jr = min(jr, c);
-  };
-
-  // Exact depth of Gaussian id's max-response point on this lane's ray (the
-  // same evaluation as the trace's).
   auto exact_tau = [&](uint32_t id) {
-    const double* G = A.geom + int64_t(kGeomStride) * id;
+    const double* Gm = A.geom + int64_t(kGeomStride) * id;
     double W[9], og[3];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) W[k] = G[kGeoW + k];
+    for (int k = 0; k < 9; ++k) W[k] = Gm[kGeoW + k];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) og[k] = G[kGeoOg + k];
+    for (int k = 0; k < 3; ++k) og[k] = Gm[kGeoOg + k];
     double tau, D2, xg[3];
-    ray_hit(W, og, G[kGeoD2c], d, &tau, &D2, xg);
+    ray_hit(W, og, Gm[kGeoD2c], d, &tau, &D2, xg);
     return tau;
   };
 
-  // Inserts a hit smaller than every dropped one into a ring with room:
-  // larger entries move up one slot, from the tail.
-  // (tau, id) < entry s of the ring in (depth, index) order, tu = tau
-  // rounded up to a float: rounding up is monotone, so unequal floats decide;
-  // a tie of the floats is decided on the entry's exact depth
-  auto before_entry = [&](double tau, float tu, uint32_t id, int s) {
-    const float st = s_btf[s][tid];
-    if (tu != st) return tu < st;
-    const uint32_t sid = entry_id(s);
-    return key_less(tau, id, exact_tau(sid), sid);
+  // (L,T) entry of pixel (ox + x, oy + y) = that of (ox, oy) + y w + x inside
+  // rect cap tile (Eq. 16).  Returns the address of pixel (ox, oy)'s, which
+  // may itself lie outside the rectangle.
+  constexpr int kEntryBytes = FMT == GART_LT_FULL ? 16 : FMT == GART_LT_T_ONLY ? 4
+                              : FMT == GART_LT_HALF || FMT == GART_LT_FIXED16 ? 8 : 2;
+  auto lt_origin = [&](int4 r, int64_t off, int* w) -> uint64_t {
+    const int xa = max(r.x, tx * TILE), xb = min(r.z, tx * TILE + TILE - 1);
+    const int ya = max(r.y, ty * TILE), yb = min(r.w, ty * TILE + TILE - 1);
+    *w = xb - xa + 1;
+    const int64_t e = off + int64_t(r.z - r.x + 1) * (ya - r.y) + int64_t(yb - ya + 1) * (xa - r.x) +
+                      (oy - ya) * *w + (ox - xa);
+    return reinterpret_cast<uint64_t>(A.lt) + uint64_t(e * kEntryBytes);
   };
 
-  // Inserts a hit smaller than every dropped one into a ring with room:
-  // larger entries move up one slot, from the tail.
-  auto insert = [&](double tau, float tu, uint32_t id, uint32_t cpos, double a) {
-    int j = cnt;
-    if (cnt > 0 && !(tu > tail_tf)) {  // not above the tail: find the place from the tail down
-      while (j > 0) {
-        const int s = (head + j - 1) & (KB - 1);
-        if (!before_entry(tau, tu, id, s)) break;
-        const int t = (s + 1) & (KB - 1);
-        s_btf[t][tid] = s_btf[s][tid];
-        s_balpha[t][tid] = s_balpha[s][tid];
-        s_bpos[t][tid] = s_bpos[s][tid];
-        if constexpr (!kPosOnly) s_bid[t][tid] = s_bid[s][tid];
-        --j;
+  // Smallest depth a key can stand for is below its float; the float above
+  // the key's low bits exceeds every depth it can stand for.  nb: float bits
+  // at or below the depth bound of everything not yet tested.
+  auto is_final = [&](uint32_t key, uint32_t nb) { return (key | SM) < nb; };
+  auto bound_bits = [&](float key) {
+    const uint32_t b = __float_as_uint(key * kscale);  // rounded; one ulp less is below the product
+    return b == 0u ? 0u : b - 1u;
+  };
+
+  // Payload of the lane's smallest pooled hit (any, if there is none).
+  uint4 pa;
+  uint2 pb;
+  auto load_head = [&]() {
+    const uint32_t slot = min(a[0] & SM, uint32_t(KB - 1));
+    pa = s_pa[slot * 64 + lane];
+    pb = s_pb[slot * 64 + lane];
+  };
+
+  // Composites the lane's smallest pooled hit, whose payload is loaded, and
+  // loads the payload of the next.
+  auto composite = [&]() {
+    uint32_t slot = a[0] & SM;
+    uint4 wn = s_win[pb.y % kWindow];
+    const bool tie = (a[0] ^ a[1]) <= SM;
+    const bool staged = pb.y >= win_lo && pb.y <= kPosMask;  // its addressing is in s_win
+    if (__builtin_expect(__ballot(tie || !staged) == 0, 1)) {
+#pragma unroll
+      for (int s = 0; s + 1 < KB; ++s) a[s] = a[s + 1];
+    } else {
+      int ex = 0;  // the smallest in (depth, index) order among the tied entries, which come first
+      if (tie) {
+        double bt = kInf;
+        uint32_t bid = kNoPrim;
+        const uint32_t top = a[0] & ~SM;
+#pragma unroll 1
+        for (int s = 0; s < int(cnt); ++s) {
+          uint32_t as = kEmpty;
+#pragma unroll
+          for (int t = 0; t < KB; ++t) as = t == s ? a[t] : as;
+          if ((as & ~SM) != top) break;
+          const uint32_t id = prim[s_pb[(as & SM) * 64 + lane].y & kPosMask];
+          const double t = exact_tau(id);
+          if (key_less(t, id, bt, bid)) {
+            bt = t;
+            bid = id;
+            ex = s;
+            slot = as & SM;
+          }
+        }
+        pa = s_pa[slot * 64 + lane];
+        pb = s_pb[slot * 64 + lane];
+      }
+#pragma unroll
+      for (int s = 0; s + 1 < KB; ++s) a[s] = s >= ex ? a[s + 1] : a[s];
+      if (pb.y >= win_lo && pb.y <= kPosMask) {
+        wn = s_win[pb.y % kWindow];
+      } else {
+        const uint32_t id = prim[pb.y & kPosMask];
+        int w;
+        const uint64_t at = lt_origin(*reinterpret_cast<const int4*>(A.rect + 4 * int64_t(id)), A.lt_offset[id], &w);
+        wn = make_uint4(uint32_t(at), uint32_t(at >> 32), uint32_t(w), id);
       }
     }
-    const int t = (head + j) & (KB - 1);
-    s_btf[t][tid] = tu;
-    s_balpha[t][tid] = a;
-    s_bpos[t][tid] = cpos;
-    if constexpr (!kPosOnly) s_bid[t][tid] = id;
-    if (j == cnt) tail_tf = tu;
-    if (j == 0) {
-      head_tf = tu;
-      head_a = a;
-      head_pos = cpos;
-      head_id = id;
-    }
-    ++cnt;
-  };
-
-  auto composite_front = [&]() {
-    const double a = head_a;
-    const uint32_t cpos = head_pos, id = head_id;
+    a[KB - 1] = kEmpty;
+    --cnt;
+    free_slots = free_slots << 4 | slot;
+    const uint32_t cpos = pb.y & kPosMask;
+    const uint32_t ofs = uint32_t(lane / 8) * wn.z + uint32_t(lane % 8);
+    void* const lt = reinterpret_cast<void*>((uint64_t(wn.y) << 32 | wn.x) + ofs * uint32_t(kEntryBytes));
+    const double al = __longlong_as_double(int64_t(uint64_t(pa.y) << 32 | pa.x));
+    const float c[3] = {max_zero(__uint_as_float(pa.z)), max_zero(__uint_as_float(pa.w)),
+                        max_zero(__uint_as_float(pb.x))};
+    load_head();
     visited = max(visited, cpos + 1u);
-    const float* shp = A.sh + int64_t(id) * (3 * K);
-    const int4 rr = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(id));
-    const int64_t e = A.lt_offset[id] + lt_local_index(rr.x, rr.y, rr.z, rr.w, TILE, px, py);
-    float c[3] = {0.5f, 0.5f, 0.5f};
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-      for (int ch = 0; ch < 3; ++ch) c[ch] = fmaf(shp[3 * k + ch], Y[k], c[ch]);
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) c[ch] = fmaxf(c[ch], 0.0f);
     // k-th composited hit of this pixel -> its list position (read by the
     // gather backward)
-    A.hit_list[int64_t(NT) * (hl_beg + min(n_hits, hl_last)) + tid] = cpos;
+    hl[uint64_t(min(n_hits, hl_last)) * NT + q_tile] = cpos;
     if constexpr (FMT == GART_LT_FULL) {
-      A.lt[e] = make_uint4(color_fixed(L0, A.inv_color_step), color_fixed(L1, A.inv_color_step),
-                           color_fixed(L2, A.inv_color_step), __float_as_uint(float(T)));
+      *static_cast<uint4*>(lt) = make_uint4(color_fixed_fma(L0, A.inv_color_step), color_fixed_fma(L1, A.inv_color_step),
+                           color_fixed_fma(L2, A.inv_color_step), __float_as_uint(float(T)));
     } else if constexpr (FMT == GART_LT_T_ONLY) {
-      reinterpret_cast<float*>(A.lt)[e] = float(T);
+      *static_cast<float*>(lt) = float(T);
     } else if constexpr (FMT == GART_LT_HALF) {
-      reinterpret_cast<uint2*>(A.lt)[e] = make_uint2(half_bits(float(L0)) | (half_bits(float(L1)) << 16),
+      *static_cast<uint2*>(lt) = make_uint2(half_bits(float(L0)) | (half_bits(float(L1)) << 16),
                                                      half_bits(float(L2)) | (half_bits(float(T)) << 16));
     } else if constexpr (FMT == GART_LT_FIXED16) {
       const double inv16 = A.inv_color_step * (1.0 / 65536.0);
-      reinterpret_cast<uint2*>(A.lt)[e] = make_uint2(
-          min(color_fixed(L0, inv16), 65535u) | (min(color_fixed(L1, inv16), 65535u) << 16),
-          min(color_fixed(L2, inv16), 65535u) | (t_log16(float(T)) << 16));
+      *static_cast<uint2*>(lt) = make_uint2(
+          min(color_fixed_fma(L0, inv16), 65535u) | (min(color_fixed_fma(L1, inv16), 65535u) << 16),
+          min(color_fixed_fma(L2, inv16), 65535u) | (t_log16(float(T)) << 16));
     } else if constexpr (FMT == GART_LT_T_LOG16) {
-      reinterpret_cast<uint16_t*>(A.lt)[e] = uint16_t(t_log16(float(T)));
+      *static_cast<uint16_t*>(lt) = uint16_t(t_log16(float(T)));
     } else {
-      reinterpret_cast<uint16_t*>(A.lt)[e] = uint16_t(half_bits(float(T)));
+      *static_cast<uint16_t*>(lt) = uint16_t(half_bits(float(T)));
     }
-    const double w = T * a;
+    const double w = T * al;
     L0 = fma(w, double(c[0]), L0);
     L1 = fma(w, double(c[1]), L1);
     L2 = fma(w, double(c[2]), L2);
-    T = T * (1.0 - a);
+    T = T * (1.0 - al);
     ++n_hits;
-    last_id = id;
-    if (T < A.t_min) {  // terminated; its exact depth is found after the trace
-      done = true;
-      end_id = id;
-    }
-    head = (head + 1) & (KB - 1);
-    --cnt;
-    if (cnt > 0) {
-      head_tf = s_btf[head][tid];
-      head_a = s_balpha[head][tid];
-      head_pos = s_bpos[head][tid];
-      head_id = entry_id(head);
-    } else {
-      head_tf = __int_as_float(0x7f800000);
-    }
+    last_id = wn.w;
+  };
+
+  // A hit into the pool (which has room): payload, then the key by a chain of
+  // medians (each entry: the middle of itself, its lower neighbour and x).
+  auto payload = [&](double alpha, float c0, float c1, float c2, uint32_t cpos, uint4* pa, uint2* pb) {
+    const uint64_t ab = uint64_t(__double_as_longlong(alpha));
+    *pa = make_uint4(uint32_t(ab), uint32_t(ab >> 32), __float_as_uint(c0), __float_as_uint(c1));
+    *pb = make_uint2(__float_as_uint(c2), cpos);
+  };
+  auto sort_in = [&](uint32_t x) {
+#pragma unroll
+    for (int s = KB - 1; s >= 1; --s) a[s] = max(min(a[s], x), min(max(a[s], x), a[s - 1]));
+    a[0] = min(a[0], x);
+  };
+  auto insert = [&](uint32_t key, double alpha, float c0, float c1, float c2, uint32_t cpos) {
+    const uint32_t slot = uint32_t(free_slots) & SM;
+    payload(alpha, c0, c1, c2, cpos, &s_pa[slot * 64 + lane], &s_pb[slot * 64 + lane]);
+    free_slots >>= 4;
+    ++cnt;
+    sort_in(key | slot);
+  };
+
+  // The chunk of the list after the current one, a position per lane.
+  int4 nx_rect;
+  int64_t nx_off;
+  float nx_key, nx_key_end;
+  uint32_t nx_id, nx2_id;
+  auto load_id = [&](int p0) { return prim[min(p0 + lane, n - 1)]; };
+  auto load_chunk = [&](int p0) {  // of the candidates nx_id from list position p0 on
+    nx_rect = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(nx_id));
+    nx_off = A.lt_offset[nx_id];
+    nx_key = pkey[min(p0 + lane, n - 1)];
+    nx_key_end = pkey[min(p0 + kChunk, n - 1)];
+  };
+  // The rows of the group after the current one: lane 16 c + v loads double v
+  // of candidate c, lane 4 k + c the SH coefficient k of candidate c.
+  double nx_row;
+  float nx_sh[3];
+  auto load_rows = [&](uint32_t ids, int g) {  // ids: one per lane, the group starts at lane g
+    nx_row = A.geom[int64_t(kGeomStride) * uint32_t(__shfl(int(ids), min(g + lane / 16, 63))) + lane % 16];
+    const uint32_t id = __shfl(int(ids), min(g + lane % 4, 63));
+    const float* sp = A.sh + (int64_t(id) * K + (K == 16 ? lane / 4 : min(lane / 4, K - 1))) * 3;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) nx_sh[ch] = sp[ch];
   };
 
   uint32_t restart = 0;
   int passes = 0;  // rescans so far
 
-  // One staged candidate: geometry row, rectangle and index.
-  struct Cand {
-    double W[9], og[3], D2c, sig;
-    int4 r;
-    uint32_t id;
-  };
-  auto load_cand = [&](int c) {
-    const double* row = s_row + c * kRow;
-    Cand cd;
+  // Lane states as wave masks: working lanes (neither terminated, nor at the
+  // end of their hits, nor stalled until a rescan), terminated lanes.
+  uint64_t work = __ballot(valid), term = ~work;
+  for (; n > 0;) {
+    const uint32_t hits_before = n_hits;
+    bool careful = passes > 0;  // hits may have to be skipped or dropped
+    nx_id = load_id(int(restart));
+    load_chunk(int(restart));
+    nx2_id = load_id(int(restart) + kChunk);
+    // The current chunk's candidates with a working pixel, moved to the first
+    // lanes in list order: index, pixel mask, list key, list position.
+    uint32_t c_id = 0, c_lo = 0, c_hi = 0, c_key = 0, c_pos = 0;
+    float key_end = 0.0f;  // list key after the chunk
+    int n_live = 0;
+    auto next_chunk = [&](int base) {
+      lds_order();
+      const int pos = base + lane;
+      int w;
+      const uint64_t at = lt_origin(nx_rect, nx_off, &w);
+      s_win[uint32_t(pos) % kWindow] = make_uint4(uint32_t(at), uint32_t(at >> 32), uint32_t(w), nx_id);
+      const uint64_t mask = pos < n ? rect_mask(nx_rect, ox, oy) : 0;
+      const uint64_t live = __ballot((mask & work) != 0);
+      n_live = __popcll(live);
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(live >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(live), 0u));
+      const int to = 4 * int((mask & work) != 0 ? below : uint32_t(n_live) + uint32_t(lane) - below);
+      c_id = __builtin_amdgcn_ds_permute(to, int(nx_id));
+      c_lo = __builtin_amdgcn_ds_permute(to, int(uint32_t(mask)));
+      c_hi = __builtin_amdgcn_ds_permute(to, int(uint32_t(mask >> 32)));
+      c_key = __builtin_amdgcn_ds_permute(to, __float_as_int(nx_key));
+      c_pos = __builtin_amdgcn_ds_permute(to, pos);
+      key_end = base + kChunk < n ? nx_key_end : __int_as_float(0x7f800000);
+      win_lo = uint32_t(max(base + kChunk - kWindow, 0));
+      // all of the above is done before the next loads are issued: a loaded
+      // value that stayed live past them would be copied, and so waited for,
+      // at the end of the step
+      uint32_t id2 = nx2_id;
+      asm volatile("" : "+v"(c_id), "+v"(c_lo), "+v"(c_hi), "+v"(c_key), "+v"(c_pos), "+v"(key_end), "+v"(id2));
+      nx_id = id2;
+      load_chunk(base + kChunk);
+      nx2_id = load_id(base + 2 * kChunk);
+    };
+    float sh[3] = {0.0f, 0.0f, 0.0f};  // the current group's SH coefficients
+    // Makes the loaded rows the current ones, and loads the group from lane g on.
+    auto stage = [&](int g) {
+      lds_order();
+      s_row[lane] = nx_row;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) cd.W[k] = row[k];
+      for (int ch = 0; ch < 3; ++ch) sh[ch] = nx_sh[ch];
+      asm volatile("" : "+v"(sh[0]), "+v"(sh[1]), "+v"(sh[2]));
+      load_rows(c_id, g);
+      lds_order();
+    };
+    // A group of the chunk's candidates per step; the next chunk is taken
+    // when the current one ends.
+    int base = int(restart) - kChunk, g = 0;
+    for (;;) {
+      const uint64_t my_mask = uint64_t(c_hi) << 32 | c_lo;
+      if ((__ballot((my_mask & work) != 0) >> g & 15u) != 0) {  // a candidate with a working pixel
+        uint64_t m[kGroup];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) cd.og[k] = row[9 + k];
-    cd.D2c = row[12];
-    cd.sig = row[13];
-    cd.r = *reinterpret_cast<const int4*>(row + 16);
-    cd.id = reinterpret_cast<const uint32_t*>(row + 18)[0];
-    return cd;
-  };
-
-  // Tests candidate c of the batch starting at list position base against
-  // this lane's ray, buffers a hit, and at the flush points composites the
-  // hits that are final.  Returns true when the lane leaves the batch
-  // (terminated, or stalled until a rescan).
-  auto visit = [&](const Cand& cd, int c, int nb, int64_t base) -> bool {
-    const uint32_t cpos = uint32_t(base - beg) + uint32_t(c);
-    const bool inside = (cpos >= from) & (px >= cd.r.x) & (px <= cd.r.z) & (py >= cd.r.y) & (py <= cd.r.w);
-    if (inside) {
-      ++n_tests;
-      double tau, D2, xg[3];
-      const uint32_t id = cd.id;
-      // in a rescan, hits up to the last composited one were composited before
-      if (ray_hit(cd.W, cd.og, cd.D2c, d, &tau, &D2, xg) && (passes == 0 || key_less(last_tau, last_id, tau, id))) {
-        if (!(tau < e_tau)) {
-          drop(tau, cpos);
-        } else {
-          const float tu = __double2float_ru(tau);
-          bool ins = true;
-          if (cnt == KB) {  // full: the larger of the new hit and the tail is dropped
-            const int s = (head + KB - 1) & (KB - 1);
-            if (!before_entry(tau, tu, id, s)) {
-              drop(tau, cpos);
-              ins = false;
-            } else {
-              // the tail's depth is above the float below its rounded-up bound
-              const float tf = s_btf[s][tid];  // > 0 (a hit has tau > 0)
-              drop(double(__uint_as_float(__float_as_uint(tf) - 1u)), s_bpos[s][tid]);
-              cnt = KB - 1;
-              tail_tf = s_btf[(head + KB - 2) & (KB - 1)][tid];
-            }
+        for (int i = 0; i < kGroup; ++i) m[i] = readlane64(my_mask, g + i) & work;
+        n_tests += uint32_t(__popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]));
+        f32x4 cr = {0.5f, 0.5f, 0.5f, 0.5f}, cg = cr, cb = cr;
+        sh_mfma(std::make_integer_sequence<int, K>{}, sh[0], sh[1], sh[2], Y, cr, cg, cb);
+        if (!careful) {
+          // straight-line code for the four candidates (a branch costs
+          // about as much as ten of its instructions)
+          uint32_t key[kGroup];
+          double D2[kGroup];
+          uint64_t h[kGroup];
+          uint32_t more = cnt;
+#pragma unroll
+          for (int i = 0; i < kGroup; ++i) {
+            const double* row = s_row + 16 * i;
+            double W[9], og[3];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) W[k] = row[k];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) og[k] = row[9 + k];
+            double tau, xg[3];
+            const bool hit = ray_hit(W, og, row[12], d, &tau, &D2[i], xg);
+            h[i] = __ballot(hit) & m[i];
+            key[i] = __float_as_uint(float(tau)) & ~SM;
+            more += lane_bit(h[i]) ? 1u : 0u;
           }
-          if (ins) insert(tau, tu, id, cpos, cd.sig * exp(-0.5 * D2));
+          if (__builtin_expect(__ballot(more > uint32_t(KB)) == 0, 1)) {
+#pragma unroll
+            for (int i = 0; i < kGroup; ++i) {
+              const uint32_t slot = uint32_t(free_slots) & SM;
+              uint4 pa;
+              uint2 pb;
+              payload(s_row[16 * i + 13] * exp_neg_half(D2[i], s_exp), cr[i], cg[i], cb[i],
+                      __builtin_amdgcn_readlane(int(c_pos), g + i), &pa, &pb);
+              lds_write_masked(h[i], &s_pa[slot * 64 + lane], pa, &s_pb[slot * 64 + lane], pb);
+              sort_in(lane_bit(h[i]) ? key[i] | slot : kEmpty);
+              free_slots = lane_bit(h[i]) ? free_slots >> 4 : free_slots;
+            }
+            cnt = more;
+          } else {
+            careful = true;
+          }
+        }
+        if (careful) {
+#pragma unroll 1
+          for (int i = 0; i < kGroup; ++i, cr = rot(cr), cg = rot(cg), cb = rot(cb)) {
+            const uint64_t mi = readlane64(my_mask, g + i) & work;
+            const uint32_t cpos = __builtin_amdgcn_readlane(int(c_pos), g + i);
+            const double* row = s_row + 16 * i;
+            double W[9], og[3];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) W[k] = row[k];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) og[k] = row[9 + k];
+            double tau, D2, xg[3];
+            bool hit = ray_hit(W, og, row[12], d, &tau, &D2, xg) && lane_bit(mi);
+            // in a rescan, hits up to the last composited one were composited before
+            const uint32_t id = __builtin_amdgcn_readlane(int(c_id), g + i);
+            hit = hit && cpos >= from && key_less(last_tau, last_id, tau, id);
+            const uint32_t key = __float_as_uint(float(tau)) & ~SM;
+            if (hit && key >= e_key) {
+              ++n_drops;
+              jr = min(jr, cpos);
+              hit = false;
+            }
+            if (hit && cnt == uint32_t(KB)) {
+              // a full pool: the hits of the largest key are dropped
+              const uint32_t top = max(a[KB - 1] & ~SM, key);
+              e_key = top;
+              if (key == top) {
+                ++n_drops;
+                jr = min(jr, cpos);
+                hit = false;
+              }
+#pragma unroll
+              for (int s = KB - 1; s >= 0; --s) {
+                if (a[s] < kEmpty && a[s] >= top) {
+                  ++n_drops;
+                  jr = min(jr, s_pb[(a[s] & SM) * 64 + lane].y & kPosMask);
+                  free_slots = free_slots << 4 | (a[s] & SM);
+                  --cnt;
+                  a[s] = kEmpty;
+                }
+              }
+            }
+            if (hit) insert(key, row[13] * exp_neg_half(D2, s_exp), cr[0], cg[0], cb[0], cpos);
+          }
         }
       }
+      // everything after the group: the next candidate, or the next chunk
+      const uint32_t nb = n_live == 0 ? 0u : bound_bits(g + kGroup < n_live ? __uint_as_float(__builtin_amdgcn_readlane(int(c_key), min(g + kGroup, 63))) : key_end);
+      // The next group's rows are waited for here, between the tests and the
+      // stores of the compositing (loads and stores complete in issue order).
+      g += kGroup;
+      if (g >= n_live) {
+        do {
+          base += kChunk;
+          next_chunk(base);
+        } while (n_live == 0 && base + kChunk < n);
+        g = 0;
+        load_rows(c_id, 0);
+      }
+      stage(g + kGroup);
+      // Composite final hits only while some lane needs the room, so that
+      // each step serves many lanes (at 1M Gaussians 60 steps a tile, each for
+      // 41 of 64 lanes on average).
+      load_head();
+      for (;;) {
+        const bool rdy = is_final(a[0], nb) && !lane_bit(term);
+        if (__ballot(rdy && cnt > uint32_t(KB - kPoolSpare)) == 0) break;
+        if (rdy) composite();
+        term |= __ballot(T < A.t_min);
+      }
+      work &= ~(term | __ballot(e_key != UINT_MAX && nb > (e_key | SM) + 1u));
+      if (n_live == 0 || work == 0) break;
     }
-    // Composite the final hits every kFlushEvery Gaussians, at the end of a
-    // batch, and whenever a lane's ring is full -- for every lane of the wave
-    // at once, so that each compositing step serves more lanes.
-    if (__ballot((c + 1) % kFlushEvery == 0 || c + 1 == nb || cnt == KB) != 0) {
-      const double nk = double(s_key[c + 1]) * kscale;
-      while (cnt > 0 && !done && double(head_tf) < nk) composite_front();
-      if (done) return true;
-      if (e_tau < kInf && nk > e_tau) {
-        stalled = true;
-        return true;
-      }
+    // End of the pass (the list's end, or no working lane): every pooled hit
+    // is below the smallest dropped one, and no unscanned Gaussian can
+    // precede it.
+    for (load_head(); __ballot(cnt != 0 && !lane_bit(term)) != 0; term |= __ballot(T < A.t_min)) {
+      if (cnt != 0 && !lane_bit(term)) composite();
     }
-    return false;
-  };
-
-  for (;;) {
-    for (int64_t base = beg + restart; base < end; base += NB) {
-      const int nb = int(min<int64_t>(NB, end - base));
-      if (tid < nb) {
-        const uint32_t id = A.pair_prim[base + tid];
-        const double* G = A.geom + int64_t(kGeomStride) * id;
-        double* row = s_row + tid * kRow;
-#pragma unroll
-        for (int k = 0; k < 15; ++k) row[k] = G[k];
-        row[15] = __longlong_as_double(A.lt_offset[id]);
-        const int4 r = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(id));
-        int* ri = reinterpret_cast<int*>(row + 16);
-        ri[0] = r.x;
-        ri[1] = r.y;
-        ri[2] = r.z;
-        ri[3] = r.w;
-        reinterpret_cast<uint32_t*>(row + 18)[0] = id;
-        s_key[tid] = A.pair_key[base + tid];
-      }
-      if (tid == 0) {
-        const int64_t nx = base + nb;
-        s_key[nb] = (nx < end) ? A.pair_key[nx] : __int_as_float(0x7f800000);
-      }
-      __syncthreads();
-      if (!done && !finished && !stalled) {
-        for (int c = 0; c < nb; ++c) {
-          // The candidate's whole staged row is read at once (one LDS round
-          // trip; every lane reads the same address), then the rectangle
-          // decides which lanes test it.
-          Cand cd = load_cand(c);
-          // materialise the row here, so that the compiler does not sink its
-          // reads into the branch (a second LDS round trip per candidate)
-#pragma unroll
-          for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(cd.W[k]));
-#pragma unroll
-          for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(cd.og[k]));
-          asm volatile("" : "+v"(cd.D2c), "+v"(cd.sig), "+v"(cd.id));
-          if (visit(cd, c, nb, base)) break;
-        }
-      }
-      const bool busy = !done && !finished && !stalled;
-      if (!__syncthreads_or(busy)) break;
-    }
-    // End of pass: every buffered hit is below the smallest dropped one and
-    // no unscanned Gaussian can precede it.
-    while (cnt > 0 && !done) composite_front();
-    const bool need = !done && !finished && e_tau < kInf;
-    if (!done && !need) finished = true;
-    if (tid == 0) s_restart = UINT_MAX;
-    __syncthreads();
-    if (need) atomicMin(&s_restart, jr);
-    __syncthreads();
-    const unsigned rs = s_restart;
-    __syncthreads();
-    if (rs == UINT_MAX) break;
+    const bool need = e_key != UINT_MAX && !lane_bit(term);
+    if (__ballot(need) == 0) break;
     if (passes >= kMaxPasses) {  // never expected: reported, not hidden
-      if (tid == 0) atomicOr(A.status, unsigned(GART_FRAME_FORWARD_INCOMPLETE));
+      if (lane == 0) atomicOr(A.status, unsigned(GART_FRAME_FORWARD_INCOMPLETE));
       break;
     }
-    restart = rs;
-    ++passes;
+    uint32_t rs = need ? jr : UINT_MAX;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) rs = min(rs, uint32_t(__shfl_xor(int(rs), off)));
+    restart = __builtin_amdgcn_readfirstlane(int(rs));
     if (need) {
       from = jr;
-      e_tau = kInf;
-      jr = UINT_MAX;
-      stalled = false;
-      cnt = 0;
-      head = 0;
-      head_tf = __int_as_float(0x7f800000);
       last_tau = n_hits ? exact_tau(last_id) : -kInf;  // for the skip test of the rescan
     }
+    // A lane that composited nothing in this pass had a whole pool of hits
+    // with one key (for instance copies of one Gaussian): its next hit is
+    // found by a scan on exact depths, and pooled as the first of the next pass.
+    const bool one = need && n_hits == hits_before;
+    if (__ballot(one) != 0) {
+      double bt = kInf, bD2 = 0.0;
+      uint32_t bid = kNoPrim, bpos = 0;
+      for (int p = int(restart); p < n; ++p) {
+        const uint32_t id = __builtin_amdgcn_readfirstlane(int(prim[p]));
+        const double kd = double(pkey[p]) * double(kscale);
+        if (__ballot(one && kd <= bt) == 0) break;
+        const int4 r = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(id));
+        if (!one || px < r.x || px > r.z || py < r.y || py > r.w) continue;
+        const double* Gm = A.geom + int64_t(kGeomStride) * id;
+        double W[9], og[3], tau, D2, xg[3];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) W[k] = Gm[k];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) og[k] = Gm[kGeoOg + k];
+        if (ray_hit(W, og, Gm[kGeoD2c], d, &tau, &D2, xg) && key_less(last_tau, last_id, tau, id) &&
+            key_less(tau, id, bt, bid)) {
+          bt = tau;
+          bD2 = D2;
+          bid = id;
+          bpos = uint32_t(p);
+        }
+      }
+      if (one && bid != kNoPrim) {
+        const float* sp = A.sh + int64_t(bid) * (3 * K);
+        float c[3] = {0.5f, 0.5f, 0.5f};
+        for (int k = 0; k < K; ++k)
+          for (int ch = 0; ch < 3; ++ch) c[ch] = fmaf(sp[3 * k + ch], Y[k], c[ch]);
+        insert(0u, A.geom[int64_t(kGeomStride) * bid + kGeoSigma] * exp_neg_half(bD2, s_exp), c[0], c[1], c[2],
+               bpos | ~kPosMask);
+        last_tau = bt;
+        last_id = bid;
+      }
+    }
+    ++passes;
+    e_key = UINT_MAX;
+    jr = UINT_MAX;
+    term |= __ballot(T < A.t_min);
+    work = __ballot(need) & ~term;
   }
 
-  // the tile's visited prefix for the backward: the block's largest
-  __shared__ uint32_t s_visited;
-  if (tid == 0) s_visited = 0;
-  __syncthreads();
+  // the wave's visited prefix for the backward: its largest
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) visited = max(visited, uint32_t(__shfl_xor(int(visited), off)));
-  if (lane_id() == 0) atomicMax(&s_visited, visited);
-  __syncthreads();
-  if (tid == 0) A.tile_visit[tile] = s_visited;
-  if (end_id != kNoPrim) end_tau = exact_tau(end_id);
-  if (__ballot(n_hits > hl_last + 1u) != 0 && lane_id() == 0) atomicOr(A.status, unsigned(GART_FRAME_HIT_LIST_FULL));
+  if (lane == 0) A.tile_visit[tile * G + grp] = visited;
+  double end_tau = kInf;
+  uint32_t end_id = kNoPrim;
+  if (valid && T < A.t_min) {  // terminated at its last hit
+    end_id = last_id;
+    end_tau = exact_tau(end_id);
+  }
+  if (__ballot(n_hits > hl_last + 1u) != 0 && lane == 0) atomicOr(A.status, unsigned(GART_FRAME_HIT_LIST_FULL));
   if (valid) {
     const int64_t p = int64_t(py) * A.cam.W + px;
     A.image[3 * p + 0] = float(L0);
@@ -412,41 +680,43 @@ __global__ GART_FWD_LAUNCH_BOUNDS(TILE* TILE) void forward_kernel(ForwardArgs A)
     st.tau_end = end_tau;
     st.id_end = end_id;
     st.n_hits = n_hits;
-    st.color_fixed[0] = color_fixed(L0, A.inv_color_step);
-    st.color_fixed[1] = color_fixed(L1, A.inv_color_step);
-    st.color_fixed[2] = color_fixed(L2, A.inv_color_step);
+    st.color_fixed[0] = color_fixed_fma(L0, A.inv_color_step);
+    st.color_fixed[1] = color_fixed_fma(L1, A.inv_color_step);
+    st.color_fixed[2] = color_fixed_fma(L2, A.inv_color_step);
     st.t_final = float(T);
     A.pixel_state[p] = st;
   }
   if (A.counters) {
     count_add(A.counters + GART_CNT_FWD_HITS, n_hits);
-    count_add(A.counters + GART_CNT_FWD_TESTS, n_tests);
+    count_add(A.counters + GART_CNT_FWD_TESTS, lane == 0 ? n_tests : 0u);
     count_add(A.counters + GART_CNT_FWD_DROPS, n_drops);
-    if (tid == 0 && passes)
+    if (lane == 0 && passes)
       atomicAdd(reinterpret_cast<unsigned long long*>(A.counters + GART_CNT_FWD_RESCANS), (unsigned long long)passes);
   }
 }
 
-// Ring sizes: deep frames (long tile lists, many pending hits per ray) get
-// the larger ring; it costs occupancy (LDS), so others get the smaller.
-#ifndef GART_FWD_RING_SMALL
-#define GART_FWD_RING_SMALL 8
-#endif
-#ifndef GART_FWD_RING_LARGE
-#define GART_FWD_RING_LARGE 16
-#endif
+// Pool sizes, by what a pool holds and what its LDS (1.5 KB an entry) costs in
+// resident waves.  8x8 tiles: 11 entries (ms at 1M / 100k Gaussians: 8: 1.00 /
+// 0.38, 9: 0.95 / 0.36, 10: 0.94 / 0.36, 11: 0.93 / 0.36, 12: 0.98 / 0.39; a
+// pool that overflows costs a rescan, 1640 of them at 8 entries and 13 at 11).
+// 16x16 tiles, whose list keys bound the depths more loosely: 12 (250k, ms:
+// 10: 0.66, 11: 0.76, 12: 0.54, 14: 0.59).  Deep frames (long tile lists, many
+// pending hits per ray): 15 (150k large Gaussians, ms: 14: 6.30, 15: 5.64,
+// 16, which leaves five waves per CU instead of six: 5.82).
 constexpr int64_t kDeepListPairs = 2048;  // mean pairs per tile from which a frame counts as deep
 
 template <int TILE, int K, int KB>
-hipError_t launch_ring(const ForwardArgs& a, hipStream_t s) {
+hipError_t launch_pool(const ForwardArgs& a, hipStream_t s) {
   const int n_tiles = a.tiles_x * a.tiles_y;
+  constexpr int G = TILE * TILE / 64;
+  const int grid = G == 1 ? n_tiles : (n_tiles + 7) / 8 * 8 * G;
   switch (a.lt_format) {
-    case GART_LT_FULL: forward_kernel<TILE, K, GART_LT_FULL, KB><<<n_tiles, TILE * TILE, 0, s>>>(a); break;
-    case GART_LT_T_ONLY: forward_kernel<TILE, K, GART_LT_T_ONLY, KB><<<n_tiles, TILE * TILE, 0, s>>>(a); break;
-    case GART_LT_HALF: forward_kernel<TILE, K, GART_LT_HALF, KB><<<n_tiles, TILE * TILE, 0, s>>>(a); break;
-    case GART_LT_T_HALF: forward_kernel<TILE, K, GART_LT_T_HALF, KB><<<n_tiles, TILE * TILE, 0, s>>>(a); break;
-    case GART_LT_FIXED16: forward_kernel<TILE, K, GART_LT_FIXED16, KB><<<n_tiles, TILE * TILE, 0, s>>>(a); break;
-    case GART_LT_T_LOG16: forward_kernel<TILE, K, GART_LT_T_LOG16, KB><<<n_tiles, TILE * TILE, 0, s>>>(a); break;
+    case GART_LT_FULL: forward_kernel<TILE, K, GART_LT_FULL, KB><<<grid, 64, 0, s>>>(a); break;
+    case GART_LT_T_ONLY: forward_kernel<TILE, K, GART_LT_T_ONLY, KB><<<grid, 64, 0, s>>>(a); break;
+    case GART_LT_HALF: forward_kernel<TILE, K, GART_LT_HALF, KB><<<grid, 64, 0, s>>>(a); break;
+    case GART_LT_T_HALF: forward_kernel<TILE, K, GART_LT_T_HALF, KB><<<grid, 64, 0, s>>>(a); break;
+    case GART_LT_FIXED16: forward_kernel<TILE, K, GART_LT_FIXED16, KB><<<grid, 64, 0, s>>>(a); break;
+    case GART_LT_T_LOG16: forward_kernel<TILE, K, GART_LT_T_LOG16, KB><<<grid, 64, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -458,9 +728,7 @@ hipError_t launch_t(const ForwardArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int64_t n_tiles = int64_t(a.tiles_x) * a.tiles_y;
   const bool deep = a.pair_count > kDeepListPairs * n_tiles;
-  // 16x16 tiles hold four waves' rings per workgroup: at most 16 entries each
-  constexpr int kLarge = TILE == 8 ? GART_FWD_RING_LARGE : (GART_FWD_RING_LARGE < 16 ? GART_FWD_RING_LARGE : 16);
-  e = deep ? launch_ring<TILE, K, kLarge>(a, s) : launch_ring<TILE, K, GART_FWD_RING_SMALL>(a, s);
+  e = deep ? launch_pool<TILE, K, 15>(a, s) : launch_pool<TILE, K, TILE == 8 ? 11 : 12>(a, s);
   if (e != hipSuccess) return e;
   return record(a.ev_end, s);
 }

@@ -1,0 +1,70 @@
+"""Forward trace at the edges of its steps: list lengths around the groups of
+four, the chunks of 64 positions and the window of 128, copies of one Gaussian
+(equal depths; more of them than a lane's pool holds), and hits that stay
+pending longer than the pool and the window hold.
+
+Against the fp64 oracle, at the bars of test_gpu_parity: pixels 1e-5 (fp32
+colours of order 1), hits per pixel exact, gradients 1e-4 relative L2.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import random_tiny_scene, rel_l2, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(sc, **kw):
+    o = oracle.OracleScene(sc)
+    ren = o.render()
+    # (a margin of exactly 0 is a tie of equal depths, which the index decides on both sides)
+    ok = (ren["margin"] >= 1e-9) | (ren["margin"] == 0)
+    assert ok.mean() > 0.9
+    gpu = run_gpu(sc, **kw)
+    assert np.array_equal(gpu["n_hits"][ok], ren["n_included"][ok])
+    assert np.abs(gpu["image"].reshape(-1, 3) - ren["color"])[ok].max() <= 1e-5
+    assert np.abs(gpu["t_final"].astype(np.float64) - ren["T_final"])[ok].max() <= 1e-6
+    if ok.all():
+        ref = o.backward(sc.dl_dimage)
+        for k, v in gpu["grads"].items():
+            assert rel_l2(v, ref[k]) <= 1e-4, k
+    return gpu
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 63, 64, 65, 127, 128, 129, 260])
+def test_list_lengths(n, tile):
+    # every Gaussian covers the whole image, one tile and a ragged edge
+    sc, _, _ = random_tiny_scene(np.random.default_rng(100 + n), n, tile + 3, tile + 1, 3, tile=tile, spread=0.2,
+                                 ls_mu=-0.6, ls_sd=0.2, logit_mu=-3.5, logit_sd=0.3, high_sd=0.1)
+    gpu = _check(sc)
+    assert np.diff(gpu["tile_range"]).max() == n
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+@pytest.mark.parametrize("copies", [2, 12, 16, 40])
+def test_copies_of_one_gaussian(copies, tile):
+    """Equal depths are composited in index order, also where a lane's pool
+    cannot hold all of them."""
+    sc, _, _ = random_tiny_scene(np.random.default_rng(copies), 60, 21, 18, 1, tile=tile, spread=0.4, ls_mu=-1.5,
+                                 ls_sd=0.3, logit_mu=-2.5, logit_sd=0.3)
+    src = 7
+    at = np.random.default_rng(3).choice(60, copies, replace=False)
+    for name in ("means", "log_scales", "quats", "opacity_logits"):
+        getattr(sc, name)[at] = getattr(sc, name)[src]
+    _check(sc)
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+def test_long_pending_hits(tile):
+    """Flat Gaussians tilted against the rays: their depth varies over a tile
+    by more than the spacing of the list, so that hits stay pending past the
+    pool (rescans) and past the window of list positions."""
+    n = 400
+    sc, _, _ = random_tiny_scene(np.random.default_rng(11), n, 40, 33, 2, tile=tile, spread=0.3, ls_mu=-0.7, ls_sd=0.2,
+                                 logit_mu=-3.5, logit_sd=0.3)
+    sc.log_scales[:, 2] = -4.0
+    from paper_2608_17298_amd import gart
+    gpu = _check(sc)
+    assert gpu["counters"][gart.CNT_FWD_RESCANS] > 0 and gpu["counters"][gart.CNT_FWD_DROPS] > 0
