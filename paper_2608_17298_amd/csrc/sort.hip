@@ -260,6 +260,110 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   }
 }
 
+// ---------------------------------------------------------------------------
+// Small sorts in one launch: one block holds every pair (ITEMS per thread in
+// registers, exchanged through LDS between passes), with the same stable
+// ranking as radix_scatter_kernel.  Up to kSmallPairs: the device-wide passes
+// are bound there by their 16 launches (1000 pairs: 53 us, 4096: 57, 8192:
+// 63), while one CU's ranking grows with the pairs (13, 21 and 35 us) and with
+// 16 per thread would reach their time (16384: 66 us both).
+// ---------------------------------------------------------------------------
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / 64;
+constexpr int64_t kSmallPairs = kSmallThreads * 8;
+
+template <int ITEMS>
+__global__ __launch_bounds__(kSmallThreads) void radix_small_kernel(uint32_t* __restrict__ keys,
+                                                                    uint32_t* __restrict__ vals, int m, int bits) {
+  __shared__ uint32_t s_keys[kSmallThreads * ITEMS];
+  __shared__ uint32_t s_vals[kSmallThreads * ITEMS];
+  __shared__ uint32_t s_wave[kSmallWaves][256];
+  __shared__ uint32_t s_wsum[4];
+  const int tid = threadIdx.x, wave = tid / 64;
+  const unsigned lane = __lane_id();
+  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  const int wbase = wave * 64 * ITEMS;  // this wave's keys: order is wave, round, lane
+  uint32_t myk[ITEMS], myv[ITEMS], myr[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int j = wbase + r * 64 + int(lane);
+    myk[r] = j < m ? keys[j] : 0u;
+    myv[r] = j < m ? vals[j] : 0u;
+  }
+  for (int shift = 0; shift < bits; shift += 8) {
+#pragma unroll
+    for (int w = 0; w < kSmallWaves / 4; ++w) s_wave[4 * w + tid / 256][tid % 256] = 0;
+    __syncthreads();
+    volatile uint32_t* wcount = s_wave[wave];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      if (wbase + r * 64 >= m) break;
+      const bool valid = wbase + r * 64 + int(lane) < m;
+      const uint32_t d = (myk[r] >> shift) & 255u;
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t bal = __ballot(bit);
+        peers &= bit ? bal : ~bal;
+      }
+      const uint32_t below = __popcll(peers & lt_mask);
+      const uint32_t before = wcount[d];
+      myr[r] = before + below;
+      if (valid && below == 0) wcount[d] = before + uint32_t(__popcll(peers));
+    }
+    __syncthreads();
+    // digit tid (first 256 threads): start over digits, then each wave's base
+    uint32_t total = 0, inc = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) total += s_wave[w][tid];
+      inc = total;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(inc, off);
+        if (lane >= unsigned(off)) inc += u;
+      }
+      if (lane == 63) s_wsum[wave] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t run = inc - total;
+      for (int w = 0; w < wave; ++w) run += s_wsum[w];
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) {
+        const uint32_t c = s_wave[w][tid];
+        s_wave[w][tid] = run;
+        run += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      if (wbase + r * 64 + int(lane) < m) {
+        const uint32_t pos = s_wave[wave][(myk[r] >> shift) & 255u] + myr[r];
+        s_keys[pos] = myk[r];
+        s_vals[pos] = myv[r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const int j = wbase + r * 64 + int(lane);
+      myk[r] = j < m ? s_keys[j] : 0u;
+      myv[r] = j < m ? s_vals[j] : 0u;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int j = wbase + r * 64 + int(lane);
+    if (j < m) {
+      keys[j] = myk[r];
+      vals[j] = myv[r];
+    }
+  }
+}
+
 __global__ void copy_pairs_kernel(const uint32_t* __restrict__ ka, const uint32_t* __restrict__ va,
                                   uint32_t* __restrict__ kb, uint32_t* __restrict__ vb, int64_t m) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -323,6 +427,13 @@ size_t radix_tmp_bytes(int64_t m) {
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt, int64_t m, int bits,
                           void* tmp, hipStream_t s) {
   if (m <= 1 || bits <= 0) return hipSuccess;
+  if (m <= kSmallPairs) {
+    if (m <= kSmallThreads * 4)
+      radix_small_kernel<4><<<1, kSmallThreads, 0, s>>>(keys, vals, int(m), bits);
+    else
+      radix_small_kernel<8><<<1, kSmallThreads, 0, s>>>(keys, vals, int(m), bits);
+    return hipGetLastError();
+  }
   const int64_t nb = ceil_div(m, kSortTile);
   uint32_t* counts = static_cast<uint32_t*>(tmp);
   char* scan_tmp = static_cast<char*>(tmp) + ((size_t(nb) * 256 * sizeof(uint32_t) + 255) & ~size_t(255));

@@ -1,0 +1,37 @@
+"""Tile map at the sizes where the pair sort changes its path: the one-block
+sort's 4 and 8 pairs per thread (4096, 8192 pairs), the device-wide passes
+from 8193 on, and the smallest lists.  Every Gaussian covers part of
+one tile, so the number of pairs is the number of Gaussians; the order is
+checked against numpy's sort by (tile, key, index)."""
+import numpy as np
+import pytest
+
+from helpers import small_camera
+from paper_2608_17298_amd.scenes import custom_scene
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("tile,w,h", [(8, 200, 96), (16, 320, 208), (8, 8, 8)])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 1024, 4095, 4096, 4097, 8191, 8192, 8193, 20000])
+def test_pair_order(n, tile, w, h):
+    from paper_2608_17298_amd import gart
+    rng = np.random.default_rng(n)
+    cam = small_camera(w, h)
+    # a point on the ray through an inner pixel of a random tile, small enough to stay in the tile
+    tx, ty = rng.integers(0, w // tile, n), rng.integers(0, h // tile, n)
+    px, py = tx * tile + rng.integers(2, tile - 2, n), ty * tile + rng.integers(2, tile - 2, n)
+    depth = rng.choice(np.linspace(2.0, 9.0, 37), n)  # many equal depths: the index decides
+    means = np.stack([(px + 0.5 - cam.cx) / cam.fx * depth, (py + 0.5 - cam.cy) / cam.fy * depth, depth - 4.0], 1)
+    ls = np.repeat((np.log(0.2 * depth / cam.fx))[:, None], 3, 1)
+    sc = custom_scene(means, ls, np.tile([1.0, 0, 0, 0], (n, 1)), np.full(n, 2.0), np.zeros((n, 1, 3)), cam, tile=tile)
+    c, st = gart.make_camera(cam), gart.make_settings(tile)
+    f = gart.prepare(gart.Gaussians.from_scene(sc), c, st)
+    assert f.pair_count == n
+    t = f.pair_tile.cpu().numpy()[:n].astype(np.int64)
+    i = f.pair_prim.cpu().numpy()[:n].astype(np.int64)
+    k = f.pair_key.cpu().numpy()[:n]
+    assert np.array_equal(np.sort(i), np.arange(n))
+    assert np.array_equal(t, (ty * (-(-w // tile)) + tx)[i])
+    assert np.array_equal(np.lexsort((i, k, t)), np.arange(n))
+    assert np.array_equal(f.tile_range.cpu().numpy(), np.searchsorted(t, np.arange(f.tiles_x * f.tiles_y + 1)))
