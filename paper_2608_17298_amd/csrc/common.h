@@ -256,12 +256,6 @@ __device__ __forceinline__ int xcd_tile(int b, int n, int tiles_x) {
 
 __device__ __forceinline__ unsigned lane_id() { return __lane_id(); }
 
-// Non-negative colour -> the frame's fixed point (round to nearest,
-// saturating at 2^32 - 1; the colour bound keeps composited colours below).
-__device__ __forceinline__ uint32_t color_fixed(double v, double inv_step) {
-  return uint32_t(fmin(rint(v * inv_step), 4294967295.0));
-}
-
 // fp16 storage of intermediate-buffer values: float rounded to the nearest
 // fp16 (hardware conversion), and back.
 __device__ __forceinline__ uint32_t half_bits(float x) {
