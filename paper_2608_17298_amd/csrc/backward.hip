@@ -535,12 +535,41 @@ __global__ __launch_bounds__(TILE* TILE, 2) void gather_kernel(BackwardArgs A) {
 // positions; each window is walked once more (S needs every hit behind), and
 // its nonzero accumulators are written into the (pair, group) rows that the
 // SH gather filled (zeros there).
+//
+// What bounds it: LDS adds one float atomic per CU and clock (ten per hit),
+// and every lane reads its own hit's rows (19 loads a lane through one tag
+// pipe).  So the lanes of a wave walk in step by hit number, which makes
+// neighbouring pixels meet the same Gaussian, and those that do add up their
+// terms in registers first; and the addresses of a pixel's next hits are read
+// ahead.  333k Gaussians, 1001x667, SH degree 2 (this kernel and the SH gather
+// before it, ms): 1.87 as each lane on its own, 1.65 with the terms of 2x2
+// and 4x2 pixels added up, 1.49 also in step, 1.46 also over 8x2 pixels, 1.41
+// also with the addresses ahead.
 // ---------------------------------------------------------------------------
 template <int TILE>
 struct HybridWindow {
   static constexpr int G = TILE * TILE / 64;
   static constexpr int kWin = TILE == 8 ? 384 : 128;  // list positions per window
 };
+
+// Adds a hit's terms of the partner lane (lane xor 1, 2, 4 or 8, read by DPP
+// controls: UP by the lane without that bit, DOWN by the one with it) if both
+// lanes' owner words hold the same list position; the lane with the bit then
+// gives its terms up (owner -1).  Lanes that are not active read as -1.
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppXor8 = 0x128;  // quad_perm [1,0,3,2], [2,3,0,1], row_ror:8
+constexpr int kDppUp4 = 0x104, kDppDown4 = 0x114;                  // row_shl:4, row_shr:4
+template <int UP, int DOWN>
+__device__ __forceinline__ void merge_hits(int& owner, int has_bit, float v[10]) {
+  const int above = __builtin_amdgcn_update_dpp(-1, owner, UP, 0xf, 0xf, false);
+  const int below = UP == DOWN ? above : __builtin_amdgcn_update_dpp(-1, owner, DOWN, 0xf, 0xf, false);
+  const bool take = !has_bit && owner >= 0 && above == owner;
+#pragma unroll
+  for (int t = 0; t < 10; ++t) {
+    const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[t]), UP, 0xf, 0xf, false));
+    v[t] += take ? o : 0.0f;
+  }
+  if (has_bit && below == owner) owner = -1;
+}
 
 template <int TILE, int K, int FMT>
 __global__ __launch_bounds__(TILE* TILE) void hybrid_pixel_kernel(BackwardArgs A) {
@@ -568,6 +597,9 @@ __global__ __launch_bounds__(TILE* TILE) void hybrid_pixel_kernel(BackwardArgs A
     for (int ch = 0; ch < 3; ++ch) g[ch] = A.dl_dimage[3 * p + ch];
     nh = int(A.pixel_state[p].n_hits);
   }
+  int nh_wave = nh;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) nh_wave = max(nh_wave, __shfl_xor(nh_wave, off));
   const int64_t beg = A.tile_range[tile];
   const uint32_t* hl = A.hit_list + int64_t(NT) * A.hl_off[tile] + tid;
   uint32_t n_walk = 0;
@@ -580,10 +612,29 @@ __global__ __launch_bounds__(TILE* TILE) void hybrid_pixel_kernel(BackwardArgs A
     __syncthreads();
     double S[3] = {0.0, 0.0, 0.0};  // colour behind the current hit
     int maxpos = -1;
-    for (int k = nh - 1; k >= 0; --k) {
-      const int pos = int(hl[int64_t(NT) * k]);
+    // Hit k is evaluated while the addresses of the hits in front of it are
+    // read ahead.
+    int pos = 0, pos1 = 0, pos2 = 0;
+    uint32_t i = 0, i1 = 0;
+    int4 r = {0, 0, 0, 0};
+    int64_t lto = 0;
+    if (nh > 0) {
+      pos = int(hl[int64_t(NT) * (nh - 1)]);
+      pos1 = int(hl[int64_t(NT) * max(nh - 2, 0)]);
+      pos2 = int(hl[int64_t(NT) * max(nh - 3, 0)]);
+      i = A.pair_prim[beg + pos];
+      i1 = A.pair_prim[beg + pos1];
+      r = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(i));
+      lto = A.lt_offset[i];
+    }
+    for (int k = nh_wave - 1; k >= 0; --k) {
+      if (k >= nh) continue;
       maxpos = max(maxpos, pos);
-      const uint32_t i = A.pair_prim[beg + pos];
+      const int pos3 = int(hl[int64_t(NT) * max(k - 3, 0)]);
+      const uint32_t i2 = A.pair_prim[beg + pos2];
+      const int4 r1 = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(i1));
+      const int64_t lto1 = A.lt_offset[i1];
+      const float T = lt_T<FMT>(lt_load<FMT>(A.lt, lto + lt_local_index(r.x, r.y, r.z, r.w, TILE, px, py)));
       const double* Gm = A.geom + int64_t(kGeomStride) * i;
       double W[9], og[3];
 #pragma unroll
@@ -592,8 +643,6 @@ __global__ __launch_bounds__(TILE* TILE) void hybrid_pixel_kernel(BackwardArgs A
       for (int e = 0; e < 3; ++e) og[e] = Gm[kGeoOg + e];
       const double sigma = Gm[kGeoSigma];
       const float oms = float(Gm[kGeoOneMinusSigma]);
-      const int4 r = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(i));
-      const float T = lt_T<FMT>(lt_load<FMT>(A.lt, A.lt_offset[i] + lt_local_index(r.x, r.y, r.z, r.w, TILE, px, py)));
       double D2, xg[3];
       hit_point(W, og, d, &D2, xg);
       const float rho = __builtin_amdgcn_exp2f(float(-0.72134752044448170368 * D2));
@@ -615,22 +664,29 @@ __global__ __launch_bounds__(TILE* TILE) void hybrid_pixel_kernel(BackwardArgs A
         const float u2 = -a * dlda;
         const float x = float(xg[0]), y = float(xg[1]), z = float(xg[2]);
         const float ux = u2 * x, uy = u2 * y, uz = u2 * z;
-        float* acc = s_acc[(pos - w0) * G + grp];
-        atomicAdd(acc + 0, ux);
-        atomicAdd(acc + 1, uy);
-        atomicAdd(acc + 2, uz);
-        atomicAdd(acc + 3, ux * x);
-        atomicAdd(acc + 4, uy * y);
-        atomicAdd(acc + 5, uz * z);
-        atomicAdd(acc + 6, ux * y);
-        atomicAdd(acc + 7, ux * z);
-        atomicAdd(acc + 8, uy * z);
-        atomicAdd(acc + 9, dlda * rho);
+        float v[10] = {ux, uy, uz, ux * x, uy * y, uz * z, ux * y, ux * z, uy * z, dlda * rho};
+        int owner = pos;  // -1 once a neighbour has taken this lane's terms
+        merge_hits<kDppXor1, kDppXor1>(owner, tid & 1, v);
+        merge_hits<kDppXor8, kDppXor8>(owner, tid & 8, v);
+        merge_hits<kDppXor2, kDppXor2>(owner, tid & 2, v);
+        merge_hits<kDppUp4, kDppDown4>(owner, tid & 4, v);
+        if (owner >= 0) {
+          float* acc = s_acc[(pos - w0) * G + grp];
+#pragma unroll
+          for (int t = 0; t < 10; ++t) atomicAdd(acc + t, v[t]);
+        }
       }
       const double wt = double(T) * double(a);
 #pragma unroll
       for (int ch = 0; ch < 3; ++ch) S[ch] = fma(wt, double(c[ch]), S[ch]);
       ++n_walk;
+      pos = pos1;
+      pos1 = pos2;
+      pos2 = pos3;
+      i = i1;
+      i1 = i2;
+      r = r1;
+      lto = lto1;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) maxpos = max(maxpos, __shfl_xor(maxpos, off));

@@ -259,9 +259,10 @@ __global__ __launch_bounds__(kBoundsBlock) void bounds_kernel(BoundsArgs A) {
 // four 16-byte loads each in flight (4 M Gaussians: 27 us with 256 threads and
 // single 8-byte loads).
 constexpr int kTotalsThreads = 1024;
-__global__ __launch_bounds__(kTotalsThreads) void bounds_totals_kernel(const unsigned long long* __restrict__ part, int64_t nb,
-                                                            const int64_t* __restrict__ area_total,
-                                                            unsigned long long* __restrict__ totals) {
+__global__ __launch_bounds__(kTotalsThreads) void bounds_totals_kernel(const unsigned long long* __restrict__ part,
+                                                                       int64_t nb,
+                                                                       const int64_t* __restrict__ area_total,
+                                                                       unsigned long long* __restrict__ totals) {
   __shared__ unsigned long long s_t[kTotalsThreads / 64];
   __shared__ float s_cb[kTotalsThreads / 64];
   unsigned long long t = 0;
