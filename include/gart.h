@@ -335,7 +335,7 @@ gart_status gart_build_tile_map(const gart_camera* camera, const gart_settings* 
                                 void* stream);
 
 /* Forward trace (Sec. 3.2-3.3, Eq. 3-8; Sec. 4.3 "LT buffer access").
- * One workgroup per tile, one lane per pixel.  Each ray tests the
+ * One wave per 8x8 pixels, one lane per pixel.  Each ray tests the
  * Gaussians of its tile list whose rectangle contains the pixel, orders the
  * hits by (tau, index), composites them front to back and, for every
  * composited hit of Gaussian i at pixel p in tile t, writes
