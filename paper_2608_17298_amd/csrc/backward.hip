@@ -543,7 +543,7 @@ __global__ __launch_bounds__(TILE* TILE, 2) void gather_kernel(BackwardArgs A) {
 // terms in registers first; and the addresses of a pixel's next hits are read
 // ahead.  333k Gaussians, 1001x667, SH degree 2 (this kernel and the SH gather
 // before it, ms): 1.87 as each lane on its own, 1.65 with the terms of 2x2
-// and 4x2 pixels added up, 1.49 also in step, 1.46 also over 8x2 pixels, 1.41
+// and 4x2 pixels added up, 1.49 also in step, 1.46 also over 8x2 pixels, 1.43
 // also with the addresses ahead.
 // ---------------------------------------------------------------------------
 template <int TILE>
