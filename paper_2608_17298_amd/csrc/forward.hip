@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
   const bool valid = px < A.cam.W && py < A.cam.H;
 
   // The tile's list keys are depths along the tile's axis; key k bounds the
-  // depth of a hit on this pixel's ray by k * kscale.
+  // depth of a hit on this pixel's ray by k * kscale (0: by nothing).
   double d[3];
   const float kscale = pixel_ray_scale(A.cam, valid ? px : 0, valid ? py : 0, tx, ty, TILE, d);
   float Y[K];  // SH basis of this pixel's ray
@@ -274,8 +274,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
   // at or below the depth bound of everything not yet tested.
   auto is_final = [&](uint32_t key, uint32_t nb) { return (key | SM) < nb; };
   auto bound_bits = [&](float key) {
-    const uint32_t b = __float_as_uint(key * kscale);  // rounded; one ulp less is below the product
-    return b == 0u ? 0u : b - 1u;
+    const float b = key * kscale;  // rounded; one ulp less is below the product
+    return b > 0.0f ? __float_as_uint(b) - 1u : 0u;  // 0 * inf (no scale, the list's end) bounds nothing either
   };
 
   // Payload of the lane's smallest pooled hit (any, if there is none).

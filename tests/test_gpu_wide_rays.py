@@ -1,0 +1,59 @@
+"""Images smaller than a tile and off-centre principal points: the rays of a
+tile then reach far from the direction through the tile's centre, up to a right
+angle and beyond, where a depth measured along that direction bounds nothing.
+
+Against the fp64 oracle, at the bars of test_gpu_parity: pixels 1e-5 (fp32
+colours of order 1), hits per pixel exact, gradients 1e-4 relative L2.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import random_tiny_scene, rel_l2, run_gpu
+from paper_2608_17298_amd.scenes import pinhole_camera
+
+pytestmark = pytest.mark.gpu
+
+# tile, width, height, vertical field of view, shift of the principal point in pixels
+VIEWS = [(16, 3, 3, 60, 0), (16, 4, 4, 60, 0), (16, 5, 5, 60, 0), (16, 7, 7, 60, 0), (16, 8, 8, 90, 0), (16, 9, 10, 90, 0),
+         (16, 12, 11, 90, 0), (8, 3, 3, 90, 0), (8, 4, 4, 90, 0), (8, 6, 5, 90, 0), (8, 3, 3, 60, 0), (16, 10, 7, 100, 3),
+         (8, 5, 4, 100, -2), (16, 21, 17, 110, -5), (16, 2, 2, 60, 0), (8, 2, 2, 60, 0)]
+
+
+def _scene(tile, w, h, fov, shift, n=300):
+    cam = pinhole_camera(w, h, float(fov))
+    cam.cx += shift
+    cam.cy -= 0.5 * shift
+    sc, _, _ = random_tiny_scene(np.random.default_rng(100 * w + h), n, w, h, 1, tile=tile,
+                                 spread=min(2.0 * np.tan(np.radians(fov / 2)), 2.8), ls_mu=-0.1, ls_sd=0.3,
+                                 logit_mu=-3.5, logit_sd=0.3, cam=cam)
+    return sc
+
+
+def _axis_cosines(cam, tile, px, py):
+    """c . u over 1 + |ca a| + |cb b| of pixels (px, py), c the direction through their tile's centre."""
+    a, b = (px + 0.5 - cam.cx) / cam.fx, (py + 0.5 - cam.cy) / cam.fy
+    ca, cb = ((px // tile + 0.5) * tile - cam.cx) / cam.fx, ((py // tile + 0.5) * tile - cam.cy) / cam.fy
+    return (1 + ca * a + cb * b) / (1 + np.abs(ca * a) + np.abs(cb * b))
+
+
+def test_views_reach_both_sides():
+    cu = np.concatenate([_axis_cosines(_scene(*v, n=1).camera, v[0], *np.meshgrid(np.arange(v[1]), np.arange(v[2]))).ravel()
+                         for v in VIEWS])
+    assert (cu < -0.1).sum() > 10 and (np.abs(cu) < 0.125).sum() > 10 and (cu > 0.5).sum() > 100
+
+
+@pytest.mark.parametrize("tile,w,h,fov,shift", VIEWS)
+def test_wide_rays(tile, w, h, fov, shift):
+    sc = _scene(tile, w, h, fov, shift)
+    o = oracle.OracleScene(sc)
+    ren = o.render()
+    assert (ren["margin"] >= 1e-9).all()
+    assert np.median(ren["n_included"]) > 20  # far more hits than a lane's pool holds
+    gpu = run_gpu(sc)
+    assert np.array_equal(gpu["n_hits"], ren["n_included"])
+    assert np.abs(gpu["image"].reshape(-1, 3) - ren["color"]).max() <= 1e-5
+    assert np.abs(gpu["t_final"].astype(np.float64) - ren["T_final"]).max() <= 1e-6
+    ref = o.backward(sc.dl_dimage)
+    for k, v in gpu["grads"].items():
+        assert rel_l2(v, ref[k]) <= 1e-4, k
