@@ -167,8 +167,11 @@ typedef struct {
                              s_q = |R^T u_q| / (c . u_q), u_q = ((x + 1/2 - cx)/fx, (y + 1/2 - cy)/fy, 1),
                              and c is the unit camera-space direction through the tile centre
                              (pixel ((tx + 1/2) tile, (ty + 1/2) tile)): the depth measured along c
-                             (s_q - 1 < 2e-5 on 8x8 tiles); each tile's list is sorted ascending by
-                             it, then by Gaussian index */
+                             (s_q - 1 < 2e-5 on 8x8 tiles of ordinary views); 0, which bounds every
+                             depth, where c . u_q of one of these rays is not above an eighth of the
+                             absolute values of its terms (images smaller than a tile, very wide
+                             angles); each tile's list is sorted ascending by it, then by Gaussian
+                             index */
   int64_t* tile_range;    /* [n_tiles+1] pairs of tile t are [tile_range[t], tile_range[t+1]) */
   /* written by gart_forward, read by gart_backward */
   int64_t lt_capacity;    /* number of intermediate entries allocated, each of

@@ -334,7 +334,9 @@ __device__ __forceinline__ float depth_code_value(uint32_t c, int bits) {
 // vertex: the smallest N / D over the four corners is the exact minimum over
 // the tile's rays.  The key is that minimum less 1e-12 relative (the forward
 // evaluates tau another way), and at least the Gaussian's own bound on tau
-// divided by the largest corner s; a hit needs tau > 0.
+// divided by the largest corner s; a hit needs tau > 0.  All of this needs
+// c . u > 0 at the four corners (and so between them): where axis_sees does not
+// hold for one of them, the key is 0, which bounds every hit.
 constexpr int kEmitGaussians = 256;
 
 __global__ __launch_bounds__(256) void emit_pairs_kernel(TileMapArgs A) {
@@ -402,7 +404,7 @@ __global__ __launch_bounds__(256) void emit_pairs_kernel(TileMapArgs A) {
     const double* Q = s_q[k];
     // The corner with the smallest N (c . u) / D and the one with the
     // largest s = |R^T u| / (c . u) are chosen by cross-multiplied
-    // comparisons (D, c . u > 0), so that one quotient (and one reciprocal
+    // comparisons (D > 0, and c . u > 0 where the result is used), so that one quotient (and one reciprocal
     // root) per pair forms each value; a choice or a value off by rounding
     // moves the bound by about 1e-15 relative, inside the 1e-12 margin below.
     // The refined estimates in place of correctly rounded operations: 98 to
@@ -433,7 +435,10 @@ __global__ __launch_bounds__(256) void emit_pairs_kernel(TileMapArgs A) {
     const double kmin = quotient(kn, kd);
     const double tk = kmin > 0.0 ? kmin - 1e-12 * kmin : 0.0;
     const double own = Q[9] * sc * inv_sqrt(sw) * (1.0 - 1e-12);
-    const double bound = fmax(own, tk);
+    const float c0 = float(cax[0]), c1 = float(cax[1]);
+    const bool seen = axis_sees(float(cax[2]), fminf(c0 * float(ax[0]), c0 * float(ax[1])),
+                                fminf(c1 * float(by[0]), c1 * float(by[1])));
+    const double bound = seen ? fmax(own, tk) : 0.0;
     A.keys[j] = (uint32_t(ty * A.tiles_x + tx) << A.key_bits) | depth_code(bound, A.key_bits);
     A.vals[j] = uint32_t(i0 + k);
   }

@@ -111,20 +111,21 @@ __device__ __forceinline__ double key_scale(const CamParams& cam, const double c
   return sqrt(w2) / fma(c[0], a, fma(c[1], b, c[2])) * (1.0 - 0x1p-40);
 }
 
-// Whether c . u = cu, a sum of terms of absolute values up to m = 1 + |ca a| +
-// |cb b|, is positive and clear of cancellation.  It is not for a ray far from
-// its tile's axis (focal lengths below about half a tile, or a tile whose
-// centre lies far outside the image): there s = |R^T u| / (c . u) is negative,
-// infinite or inaccurate, and depths along c order nothing.
-template <typename F>
-__device__ __forceinline__ bool axis_sees(F cu, F m) {
-  return cu > F(0.125) * m;
+// Whether c . u = c2 + p + q (c2 > 0, p and q the terms along the image axes)
+// is positive and clear of cancellation: above an eighth of the terms' absolute
+// values.  It is not for a ray far from its tile's axis (focal lengths below
+// about half a tile, or a tile whose centre lies far outside the image): there
+// s = |R^T u| / (c . u) is negative, infinite or inaccurate, and depths along c
+// order nothing.  Monotone in p and in q, so over a rectangle of rays the
+// smallest p and q decide.
+__device__ __forceinline__ bool axis_sees(float c2, float p, float q) {
+  return fmaf(-0.125f, c2 + fabsf(p) + fabsf(q), c2 + p + q) > 0.0f;
 }
 
 // pixel_ray, and key_scale of the ray in fp32, or 0 where the ray has no
-// usable scale (a key then bounds nothing).  The relative error of c . u is at
-// most 2^-21 m / cu (eight roundings of its terms), so below 2^-18 where
-// axis_sees holds; the other factors add less than 2^-20 as long as no step
+// usable scale (a key then bounds nothing).  The error of c . u is at most 2^-21
+// of its terms' absolute values (eight roundings), so relatively below 2^-18
+// where axis_sees holds; the other factors add less than 2^-20 as long as no step
 // leaves the normal range, and the result is lowered by 2^-17, so that it
 // stays below key_scale.
 __device__ __forceinline__ float pixel_ray_scale(const CamParams& cam, int px, int py, int tx, int ty, int ts,
@@ -135,10 +136,9 @@ __device__ __forceinline__ float pixel_ray_scale(const CamParams& cam, int px, i
   const float a = float(double(px) + 0.5 - cam.cx) * ifx, b = float(double(py) + 0.5 - cam.cy) * ify;
   const float ca = float(double(tx * ts) + 0.5 * ts - cam.cx) * ifx, cb = float(double(ty * ts) + 0.5 * ts - cam.cy) * ify;
   const float cu = fmaf(ca, a, fmaf(cb, b, 1.0f));
-  const float m = 1.0f + fabsf(ca * a) + fabsf(cb * b);
   const float w2f = float(w2);
   const float s = sqrtf(w2f * fmaf(ca, ca, fmaf(cb, cb, 1.0f))) / cu * (1.0f - 0x1p-17f);
-  return axis_sees(cu, m) && w2f > 0x1p-100f && s > 0x1p-100f && s < __int_as_float(0x7f800000) ? s : 0.0f;
+  return axis_sees(1.0f, ca * a, cb * b) && w2f > 0x1p-100f && s > 0x1p-100f && s < __int_as_float(0x7f800000) ? s : 0.0f;
 }
 
 // Max-response point of a Gaussian on the ray o + tau d (Eq. 4-5) in the

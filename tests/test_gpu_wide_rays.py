@@ -43,17 +43,49 @@ def test_views_reach_both_sides():
     assert (cu < -0.1).sum() > 10 and (np.abs(cu) < 0.125).sum() > 10 and (cu > 0.5).sum() > 100
 
 
+@pytest.mark.parametrize("mode", ["gather", "scatter"])  # scatter: ends a ray's list by its keys too
 @pytest.mark.parametrize("tile,w,h,fov,shift", VIEWS)
-def test_wide_rays(tile, w, h, fov, shift):
+def test_wide_rays(tile, w, h, fov, shift, mode):
     sc = _scene(tile, w, h, fov, shift)
     o = oracle.OracleScene(sc)
     ren = o.render()
     assert (ren["margin"] >= 1e-9).all()
     assert np.median(ren["n_included"]) > 20  # far more hits than a lane's pool holds
-    gpu = run_gpu(sc)
+    gpu = run_gpu(sc, mode=mode)
     assert np.array_equal(gpu["n_hits"], ren["n_included"])
     assert np.abs(gpu["image"].reshape(-1, 3) - ren["color"]).max() <= 1e-5
     assert np.abs(gpu["t_final"].astype(np.float64) - ren["T_final"]).max() <= 1e-6
     ref = o.backward(sc.dl_dimage)
     for k, v in gpu["grads"].items():
         assert rel_l2(v, ref[k]) <= 1e-4, k
+
+
+@pytest.mark.parametrize("tile,w,h,fov,shift", VIEWS)
+def test_pair_keys_bound_every_hit(tile, w, h, fov, shift):
+    """A pair's key is at most tau_q / s_q at every hit whose ray the tile's
+    axis sees, and 0 if its Gaussian's rectangle holds a ray that it does not."""
+    sc = _scene(tile, w, h, fov, shift)
+    o = oracle.OracleScene(sc)
+    rect = o.prim_info().rect
+    gpu = run_gpu(sc)
+    cam, tx_n = sc.camera, -(-w // tile)
+    cu_all = _axis_cosines(cam, tile, *np.meshgrid(np.arange(w), np.arange(h)))
+    positive = 0
+    for t, i, key in zip(gpu["pair_tile"].astype(int), gpu["pair_prim"].astype(int), gpu["pair_key"].astype(np.float64)):
+        tx, ty = t % tx_n, t // tx_n
+        x0, y0, x1, y1 = rect[i]
+        xs = np.arange(max(x0, tx * tile), min(x1, tx * tile + tile - 1) + 1)
+        ys = np.arange(max(y0, ty * tile), min(y1, ty * tile + tile - 1) + 1)
+        px, py = (v.ravel() for v in np.meshgrid(xs, ys))
+        cu = cu_all[py, px]
+        if (cu <= 0.125).any():
+            assert key == 0
+            continue
+        positive += key > 0
+        r = o.ray_prim(py * w + px, np.full(px.size, i))
+        u = np.stack([(px + 0.5 - cam.cx) / cam.fx, (py + 0.5 - cam.cy) / cam.fy, np.ones(px.size)], 1)
+        c = np.array([((tx + 0.5) * tile - cam.cx) / cam.fx, ((ty + 0.5) * tile - cam.cy) / cam.fy, 1.0])
+        s_q = np.linalg.norm(u @ np.asarray(cam.R, np.float64), axis=1) / (u @ (c / np.linalg.norm(c)))
+        hit = r["hit"].astype(bool)
+        assert np.all(key <= (r["tau"] / s_q)[hit])
+    assert positive > 0 or (cu_all <= 0.125).any()
