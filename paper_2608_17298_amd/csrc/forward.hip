@@ -32,9 +32,12 @@
 // the compositing (ms): 1M Gaussians 1.47 -> 0.93, 4M 2.52 -> 1.56, 100k 0.57
 // -> 0.36, 150k large 9.9 -> 5.64, 250k on 16x16 tiles 1.91 -> 0.54, 4k 0.41
 // -> 0.12.
-// If a pool overflows, its largest hits are dropped and the lane later
+// If a pool overflows, its largest hit in (depth, index) order is dropped --
+// exact depths, recomputed, decide between equal keys -- and the lane later
 // rescans the list from the first Gaussian it dropped, skipping hits already
-// composited; compositing stops once the transmittance falls below t_min.
+// composited, so that every pass composites at least a pool of hits, also where
+// all depths are equal (copies of one Gaussian, flat Gaussians in one plane);
+// compositing stops once the transmittance falls below t_min.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,8 +55,8 @@ constexpr int kChunk = 64;    // list positions looked at together, one per lane
 constexpr int kWindow = 128;  // list positions whose (L,T) addressing is kept in LDS
 constexpr int kPoolSpare = 4;  // free entries below which a lane's final hits are composited
 
-// Each rescan composites at least one hit per rescanning lane, so the pass
-// count is bounded by the hits of a tile; this cap only guards against a
+// Each pass composites at least a pool of hits per lane that rescans after it,
+// so the pass count is bounded by the hits of a tile; this cap only guards against a
 // defect turning into a hang, and is reported in the frame status if reached.
 constexpr int kMaxPasses = 1 << 20;
 
@@ -176,7 +179,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
   constexpr uint32_t SM = (1u << SB) - 1u;  // payload slot bits of a pool key
   constexpr uint32_t kEmpty = UINT_MAX;
   constexpr double kInf = __builtin_huge_val();
-  constexpr uint32_t kPosMask = 0x7fffffffu;  // list position of a payload; the top bit: found by an exact scan
   static_assert(KB >= 2 && KB <= 16, "pool slots fit the key's low bits");
 
   __shared__ __align__(16) double s_row[kGroup * 16];  // W (9), o_g (3), D2c, sigma, -, -
@@ -235,8 +237,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
   for (int s = 0; s < KB; ++s) a[s] = kEmpty;
   uint32_t cnt = 0;
   Stack free_slots = Stack(0xfedcba9876543210ull);
-  uint32_t e_key = UINT_MAX;  // smallest depth key (low bits clear) of the dropped hits; every pooled key is below it
-  uint32_t jr = UINT_MAX;     // first list position holding a dropped hit
+  // The smallest dropped hit in (depth, index) order; every pooled hit is
+  // before it.  Its depth and index are found from its list position when
+  // first needed (e_tau: NaN until then).
+  uint32_t e_key = UINT_MAX;  // its depth key (low bits clear)
+  double e_tau = kInf;
+  uint32_t e_id = kNoPrim, e_pos = 0;
+  uint32_t jr = UINT_MAX;  // first list position holding a dropped hit
   // A rescan starts the wave at the smallest jr of its lanes; a lane skips
   // the positions before its own jr (from): every hit there was composited
   // in an earlier pass.
@@ -253,6 +260,44 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
     double tau, D2, xg[3];
     ray_hit(W, og, Gm[kGeoD2c], d, &tau, &D2, xg);
     return tau;
+  };
+
+  // Among the pooled hits of key top, which are the pool's first (FIRST) or
+  // last ones: the payload slot of the smallest (FIRST) or largest one in
+  // (depth, index) order, if it is before (after) (t, i), which it replaces;
+  // else UINT_MAX.  Four ray tests at a time, for the latency of their rows (60000
+  // flat Gaussians in one plane, 116 hits a ray, ms: 59, two 53, four 48).
+  auto tied_entry = [&](auto first, uint32_t top, double& t, uint32_t& i) {
+    constexpr bool FIRST = decltype(first)::value;
+    constexpr int N = 4;
+    uint32_t slot = UINT_MAX;
+#pragma unroll 1
+    for (int s0 = 0; s0 < KB; s0 += N) {
+      uint32_t as[N], id[N];
+      double ts[N];
+      bool ok[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const int s = FIRST ? s0 + j : KB - 1 - s0 - j;
+        as[j] = kEmpty;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) as[j] = k == s ? a[k] : as[j];
+        ok[j] = as[j] != kEmpty && (as[j] & ~SM) == top;
+        const uint32_t pos = s_pb[min(as[j] & SM, uint32_t(KB - 1)) * 64 + lane].y;
+        id[j] = prim[ok[j] ? pos : 0u];
+      }
+#pragma unroll
+      for (int j = 0; j < N; ++j) ts[j] = exact_tau(id[j]);
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const bool take = ok[j] && (FIRST ? key_less(ts[j], id[j], t, i) : key_less(t, i, ts[j], id[j]));
+        slot = take ? as[j] & SM : slot;
+        t = take ? ts[j] : t;
+        i = take ? id[j] : i;
+      }
+      if (!ok[N - 1]) break;
+    }
+    return slot;
   };
 
   // (L,T) entry of pixel (ox + x, oy + y) = that of (ox, oy) + y w + x inside
@@ -293,40 +338,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
     uint32_t slot = a[0] & SM;
     uint4 wn = s_win[pb.y % kWindow];
     const bool tie = (a[0] ^ a[1]) <= SM;
-    const bool staged = pb.y >= win_lo && pb.y <= kPosMask;  // its addressing is in s_win
+    const bool staged = pb.y >= win_lo;  // its addressing is in s_win
     if (__builtin_expect(__ballot(tie || !staged) == 0, 1)) {
 #pragma unroll
       for (int s = 0; s + 1 < KB; ++s) a[s] = a[s + 1];
     } else {
-      int ex = 0;  // the smallest in (depth, index) order among the tied entries, which come first
+      bool past = true;  // the entries from this hit's on move down
       if (tie) {
         double bt = kInf;
         uint32_t bid = kNoPrim;
-        const uint32_t top = a[0] & ~SM;
-#pragma unroll 1
-        for (int s = 0; s < int(cnt); ++s) {
-          uint32_t as = kEmpty;
-#pragma unroll
-          for (int t = 0; t < KB; ++t) as = t == s ? a[t] : as;
-          if ((as & ~SM) != top) break;
-          const uint32_t id = prim[s_pb[(as & SM) * 64 + lane].y & kPosMask];
-          const double t = exact_tau(id);
-          if (key_less(t, id, bt, bid)) {
-            bt = t;
-            bid = id;
-            ex = s;
-            slot = as & SM;
-          }
-        }
+        slot = tied_entry(std::true_type{}, a[0] & ~SM, bt, bid);
+        past = false;
         pa = s_pa[slot * 64 + lane];
         pb = s_pb[slot * 64 + lane];
       }
 #pragma unroll
-      for (int s = 0; s + 1 < KB; ++s) a[s] = s >= ex ? a[s + 1] : a[s];
-      if (pb.y >= win_lo && pb.y <= kPosMask) {
+      for (int s = 0; s + 1 < KB; ++s) {
+        past = past || (a[s] & SM) == slot;
+        a[s] = past ? a[s + 1] : a[s];
+      }
+      if (pb.y >= win_lo) {
         wn = s_win[pb.y % kWindow];
       } else {
-        const uint32_t id = prim[pb.y & kPosMask];
+        const uint32_t id = prim[pb.y];
         int w;
         const uint64_t at = lt_origin(*reinterpret_cast<const int4*>(A.rect + 4 * int64_t(id)), A.lt_offset[id], &w);
         wn = make_uint4(uint32_t(at), uint32_t(at >> 32), uint32_t(w), id);
@@ -335,7 +369,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
     a[KB - 1] = kEmpty;
     --cnt;
     free_slots = free_slots << 4 | slot;
-    const uint32_t cpos = pb.y & kPosMask;
+    const uint32_t cpos = pb.y;
     const uint32_t ofs = uint32_t(lane / 8) * wn.z + uint32_t(lane % 8);
     void* const lt = reinterpret_cast<void*>((uint64_t(wn.y) << 32 | wn.x) + ofs * uint32_t(kEntryBytes));
     const double al = __longlong_as_double(int64_t(uint64_t(pa.y) << 32 | pa.x));
@@ -424,7 +458,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
   // end of their hits, nor stalled until a rescan), terminated lanes.
   uint64_t work = __ballot(valid), term = ~work;
   for (; n > 0;) {
-    const uint32_t hits_before = n_hits;
     bool careful = passes > 0;  // hits may have to be skipped or dropped
     nx_id = load_id(int(restart));
     load_chunk(int(restart));
@@ -523,6 +556,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
           }
         }
         if (careful) {
+          // one candidate at a time
 #pragma unroll 1
           for (int i = 0; i < kGroup; ++i, cr = rot(cr), cg = rot(cg), cb = rot(cb)) {
             const uint64_t mi = readlane64(my_mask, g + i) & work;
@@ -540,29 +574,53 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
             hit = hit && cpos >= from && key_less(last_tau, last_id, tau, id);
             const uint32_t key = __float_as_uint(float(tau)) & ~SM;
             if (hit && key >= e_key) {
-              ++n_drops;
-              jr = min(jr, cpos);
-              hit = false;
-            }
-            if (hit && cnt == uint32_t(KB)) {
-              // a full pool: the hits of the largest key are dropped
-              const uint32_t top = max(a[KB - 1] & ~SM, key);
-              e_key = top;
-              if (key == top) {
+              bool drop = key > e_key;
+              if (!drop) {
+                if (e_tau != e_tau) {
+                  e_id = prim[e_pos];
+                  e_tau = exact_tau(e_id);
+                }
+                drop = !key_less(tau, id, e_tau, e_id);
+              }
+              if (drop) {
                 ++n_drops;
                 jr = min(jr, cpos);
                 hit = false;
               }
+            }
+            if (hit && cnt == uint32_t(KB)) {  // a full pool: the largest of its hits and the new one is dropped
+              const uint32_t top = max(a[KB - 1] & ~SM, key);
+              bool drop_new = key == top;
+              e_tau = drop_new ? tau : __builtin_nan("");
+              e_id = id;
+              if ((a[KB - 1] & ~SM) == top && (key == top || (a[KB - 2] & ~SM) == top)) {
+                // among equal keys the exact depths decide, then the indices
+                if (key != top) e_tau = -kInf;
+                const uint32_t slot = tied_entry(std::false_type{}, top, e_tau, e_id);
+                drop_new = slot == UINT_MAX;
+                if (!drop_new) {  // to the end of the pool
+                  bool past = false;
 #pragma unroll
-              for (int s = KB - 1; s >= 0; --s) {
-                if (a[s] < kEmpty && a[s] >= top) {
-                  ++n_drops;
-                  jr = min(jr, s_pb[(a[s] & SM) * 64 + lane].y & kPosMask);
-                  free_slots = free_slots << 4 | (a[s] & SM);
-                  --cnt;
-                  a[s] = kEmpty;
+                  for (int s = 0; s + 1 < KB; ++s) {
+                    past = past || (a[s] & SM) == slot;
+                    a[s] = past ? a[s + 1] : a[s];
+                  }
+                  a[KB - 1] = top | slot;
                 }
               }
+              ++n_drops;
+              e_key = top;
+              e_pos = cpos;
+              if (drop_new) {
+                hit = false;
+              } else {
+                const uint32_t slot = a[KB - 1] & SM;
+                e_pos = s_pb[slot * 64 + lane].y;
+                free_slots = free_slots << 4 | slot;
+                a[KB - 1] = kEmpty;
+                --cnt;
+              }
+              jr = min(jr, e_pos);
             }
             if (hit) insert(key, row[13] * exp_neg_half(D2, s_exp), cr[0], cg[0], cb[0], cpos);
           }
@@ -614,44 +672,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
     if (need) {
       from = jr;
       last_tau = n_hits ? exact_tau(last_id) : -kInf;  // for the skip test of the rescan
-    }
-    // A lane that composited nothing in this pass had a whole pool of hits
-    // with one key (for instance copies of one Gaussian): its next hit is
-    // found by a scan on exact depths, and pooled as the first of the next pass.
-    const bool one = need && n_hits == hits_before;
-    if (__ballot(one) != 0) {
-      double bt = kInf, bD2 = 0.0;
-      uint32_t bid = kNoPrim, bpos = 0;
-      for (int p = int(restart); p < n; ++p) {
-        const uint32_t id = __builtin_amdgcn_readfirstlane(int(prim[p]));
-        const double kd = double(pkey[p]) * double(kscale);
-        if (__ballot(one && kd <= bt) == 0) break;
-        const int4 r = *reinterpret_cast<const int4*>(A.rect + 4 * int64_t(id));
-        if (!one || px < r.x || px > r.z || py < r.y || py > r.w) continue;
-        const double* Gm = A.geom + int64_t(kGeomStride) * id;
-        double W[9], og[3], tau, D2, xg[3];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) W[k] = Gm[k];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) og[k] = Gm[kGeoOg + k];
-        if (ray_hit(W, og, Gm[kGeoD2c], d, &tau, &D2, xg) && key_less(last_tau, last_id, tau, id) &&
-            key_less(tau, id, bt, bid)) {
-          bt = tau;
-          bD2 = D2;
-          bid = id;
-          bpos = uint32_t(p);
-        }
-      }
-      if (one && bid != kNoPrim) {
-        const float* sp = A.sh + int64_t(bid) * (3 * K);
-        float c[3] = {0.5f, 0.5f, 0.5f};
-        for (int k = 0; k < K; ++k)
-          for (int ch = 0; ch < 3; ++ch) c[ch] = fmaf(sp[3 * k + ch], Y[k], c[ch]);
-        insert(0u, A.geom[int64_t(kGeomStride) * bid + kGeoSigma] * exp_neg_half(bD2, s_exp), c[0], c[1], c[2],
-               bpos | ~kPosMask);
-        last_tau = bt;
-        last_id = bid;
-      }
     }
     ++passes;
     e_key = UINT_MAX;

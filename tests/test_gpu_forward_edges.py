@@ -68,3 +68,23 @@ def test_long_pending_hits(tile):
     from paper_2608_17298_amd import gart
     gpu = _check(sc)
     assert gpu["counters"][gart.CNT_FWD_RESCANS] > 0 and gpu["counters"][gart.CNT_FWD_DROPS] > 0
+
+
+POOL = 11  # entries of the smallest pool a lane has
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+@pytest.mark.parametrize("n,step", [(40, 0.0), (130, 0.0), (130, 2e-8), (60, 4e-7)])
+def test_equal_depths_take_few_passes(n, step, tile):
+    """Gaussians at the same depth, and closer together than the pool's keys
+    tell apart: every pass over the list composites a pool of hits a lane."""
+    sc, _, _ = random_tiny_scene(np.random.default_rng(n), n, tile + 5, tile - 1, 1, tile=tile, logit_mu=-4.0, logit_sd=0.2)
+    sc.means[:] = 0.0
+    sc.means[:, 2] = np.random.default_rng(5).permutation(n) * np.float32(step)
+    sc.log_scales[:] = [-0.2, -0.6, -0.4]
+    sc.quats[:] = sc.quats[0]
+    gpu = _check(sc)
+    from paper_2608_17298_amd import gart
+    waves = -(-(tile + 5) // 8) * -(-(tile - 1) // 8)
+    assert gpu["n_hits"].max() == n
+    assert gpu["counters"][gart.CNT_FWD_RESCANS] <= waves * (-(-n // POOL) - 1)
