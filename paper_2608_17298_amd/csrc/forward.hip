@@ -457,7 +457,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
   // Lane states as wave masks: working lanes (neither terminated, nor at the
   // end of their hits, nor stalled until a rescan), terminated lanes.
   uint64_t work = __ballot(valid), term = ~work;
-  for (; n > 0;) {
+  for (; n > 0 && work != 0;) {  // (a block of the tile may lie outside the image)
     bool careful = passes > 0;  // hits may have to be skipped or dropped
     nx_id = load_id(int(restart));
     load_chunk(int(restart));
