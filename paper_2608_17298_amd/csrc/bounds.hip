@@ -137,11 +137,18 @@ __global__ __launch_bounds__(kBoundsBlock) void bounds_kernel(BoundsArgs A) {
       if (vis) vis = axis_cover(Q(0, 0), Q(0, 2), Q44, c.W, &rx0, &rx1);
       if (vis) vis = axis_cover(Q(1, 1), Q(1, 2), Q44, c.H, &ry0, &ry1);
       if (vis) {
-        // W = S^-1 R^T, o_g = W (o - mu)
+        // W = S^-1 R^T, o_g = W (o - mu).  If every scale is beyond 2^200, W is
+        // raised by a power of two that brings the smallest there: the trace
+        // divides by squares of its entries and the pair keys compare products
+        // of two such squares, which must stay in the normal range.  Depths do
+        // not change, and D2, below 2^-140 either way (|o - mu| < 2^130), still
+        // vanishes next to 1 and to the squared clamp radius (above 2^-52).
+        const double smin = fmin(s[0], fmin(s[1], s[2]));
+        const double f = smin > 0x1p200 ? ldexp(1.0, ilogb(smin) - 200) : 1.0;
         const double om[3] = {c.o[0] - mu[0], c.o[1] - mu[1], c.o[2] - mu[2]};
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          const double is = 1.0 / s[k];
+          const double is = f / s[k];
           const double w0 = R[k] * is, w1 = R[3 + k] * is, w2 = R[6 + k] * is;
           G[kGeoW + 3 * k + 0] = w0;
           G[kGeoW + 3 * k + 1] = w1;
@@ -162,7 +169,7 @@ __global__ __launch_bounds__(kBoundsBlock) void bounds_kernel(BoundsArgs A) {
         // th = asin(r/|mu-o|) of u = (mu - o)/|mu - o|:
         //   |S R^T d| <= |S R^T u| + s_max th,  |S^-1 R^T d| <= |S^-1 R^T u| + th / s_min.
         const double dist = sqrt(om[0] * om[0] + om[1] * om[1] + om[2] * om[2]);
-        const double smax = fmax(s[0], fmax(s[1], s[2])), smin = fmin(s[0], fmin(s[1], s[2]));
+        const double smax = fmax(s[0], fmax(s[1], s[2]));
         const double r = ac * smax;
         double lo = dist - r;
         if (dist > r) {

@@ -11,6 +11,7 @@ import pytest
 
 import oracle
 from helpers import random_tiny_scene, rel_l2, run_gpu
+from paper_2608_17298_amd.scenes import pinhole_camera
 
 pytestmark = pytest.mark.gpu
 
@@ -88,3 +89,27 @@ def test_equal_depths_take_few_passes(n, step, tile):
     waves = -(-(tile + 5) // 8) * -(-(tile - 1) // 8)
     assert gpu["n_hits"].max() == n
     assert gpu["counters"][gart.CNT_FWD_RESCANS] <= waves * (-(-n // POOL) - 1)
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+def test_scales_beyond_the_square_root_of_the_range(tile):
+    """Gaussians whose squared inverse scales are subnormal, and which are still
+    visible (axis-aligned, opacity within rounding of alpha_min, so that their
+    rectangle is the image): hit by every ray, in the order of their depths."""
+    n, huge = 40, 12
+    cam = pinhole_camera(13, 11)
+    cam.cx = cam.cy = 0.0
+    rng = np.random.default_rng(1)
+    sc, _, _ = random_tiny_scene(rng, n, 13, 11, 1, tile=tile, ls_mu=-0.6, ls_sd=0.3, logit_mu=-2.0, logit_sd=0.3, cam=cam)
+    alpha_min = float(np.float32(1 / 255))
+    threshold = np.log(alpha_min / (1 - alpha_min))
+    sc.means[:huge, :2] = 0.0
+    sc.log_scales[:huge] = rng.uniform(354.0, 358.0, (huge, 3))
+    sc.quats[:huge] = [1, 0, 0, 0]
+    sc.opacity_logits[:huge] = np.float32(threshold) + np.float32(4.8e-7) * rng.integers(2, 20, huge)
+    o = oracle.OracleScene(sc)
+    assert (np.exp(-2.0 * sc.log_scales[:huge].astype(np.float64).min(1)) < np.finfo(np.float64).tiny).sum() > 6
+    assert (o.prim_info().area[:huge] == 13 * 11).sum() > 6
+    assert o.ray_prim(np.arange(13 * 11), np.zeros(13 * 11, int))["hit"].all()
+    gpu = _check(sc)
+    assert gpu["n_hits"].min() > 6
