@@ -262,8 +262,8 @@ __global__ __launch_bounds__(kBoundsBlock) void bounds_kernel(BoundsArgs A) {
   }
 }
 
-// One block adds up the blocks' partials: latency-bound, so 1024 threads with
-// four 16-byte loads each in flight (4 M Gaussians: 27 us with 256 threads and
+// One block adds up the blocks' partials (8-byte aligned, as the scratch may
+// be): latency-bound, so 1024 threads with four pairs each in flight (4 M Gaussians: 27 us with 256 threads and
 // single 8-byte loads).
 constexpr int kTotalsThreads = 1024;
 __global__ __launch_bounds__(kTotalsThreads) void bounds_totals_kernel(const unsigned long long* __restrict__ part,
@@ -276,9 +276,8 @@ __global__ __launch_bounds__(kTotalsThreads) void bounds_totals_kernel(const uns
   float cb = 0.0f;
 #pragma unroll 4
   for (int64_t b = threadIdx.x; b < nb; b += kTotalsThreads) {
-    const ulonglong2 v = reinterpret_cast<const ulonglong2*>(part)[b];
-    t += v.x;
-    cb = fmaxf(cb, __uint_as_float(uint32_t(v.y)));
+    t += part[2 * b];
+    cb = fmaxf(cb, __uint_as_float(uint32_t(part[2 * b + 1])));
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {

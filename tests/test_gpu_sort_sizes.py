@@ -2,7 +2,8 @@
 sort's 4 and 8 pairs per thread (4096, 8192 pairs), the device-wide passes
 from 8193 on, and the smallest lists.  Every Gaussian covers part of
 one tile, so the number of pairs is the number of Gaussians; the order is
-checked against numpy's sort by (tile, key, index)."""
+checked against numpy's sort by (tile, key, index).  Also a frame scratch that
+is aligned to 8 bytes only, which bounds, tile map and forward take."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,27 @@ def test_pair_order(n, tile, w, h):
     assert np.array_equal(t, (ty * (-(-w // tile)) + tx)[i])
     assert np.array_equal(np.lexsort((i, k, t)), np.arange(n))
     assert np.array_equal(f.tile_range.cpu().numpy(), np.searchsorted(t, np.arange(f.tiles_x * f.tiles_y + 1)))
+
+
+@pytest.mark.parametrize("n", [3, 300_000, 1_400_000])  # one block of partial sums, more than one load of a thread
+def test_scratch_aligned_to_8_bytes(n):
+    import torch
+    from paper_2608_17298_amd import gart
+    rng = np.random.default_rng(n)
+    cam = small_camera(64, 40)
+    sc = custom_scene(rng.uniform(-2, 2, (n, 3)), np.full((n, 3), -2.0 if n < 10 else -5.0), np.tile([1.0, 0, 0, 0], (n, 1)),
+                      np.full(n, 2.0), rng.standard_normal((n, 1, 3)), cam)
+    c, st, g = gart.make_camera(cam), gart.make_settings(8), gart.Gaussians.from_scene(sc)
+    got = []
+    for offset in (0, 8):
+        f = gart.prepare(g, c, st)
+        buf = torch.zeros(f.scratch.numel() + 16, dtype=torch.uint8, device="cuda")
+        f.scratch = buf[offset:offset + f.scratch.numel()]
+        assert f.scratch.data_ptr() % 16 == offset
+        totals = gart.gart_bounds(g, c, st, f)
+        gart.gart_build_tile_map(c, st, f)
+        image = torch.empty((cam.height, cam.width, 3), device="cuda")
+        gart.gart_forward(g, c, st, f, image)
+        got.append((totals, f.color_step, f.pair_prim.cpu().numpy()[:f.pair_count], image.cpu().numpy()))
+    assert got[0][:2] == got[1][:2] and got[0][0][1] > 0
+    assert np.array_equal(got[0][2], got[1][2]) and np.array_equal(got[0][3], got[1][3])
