@@ -175,11 +175,10 @@ template <int TILE, int K, int FMT, int KB>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void forward_kernel(ForwardArgs A) {
   constexpr int NT = TILE * TILE;
   constexpr int G = NT / 64;  // 8x8 blocks (waves) per tile
-  constexpr int SB = KB <= 8 ? 3 : 4;
-  constexpr uint32_t SM = (1u << SB) - 1u;  // payload slot bits of a pool key
+  constexpr uint32_t SM = 15u;  // payload slot bits of a pool key
   constexpr uint32_t kEmpty = UINT_MAX;
   constexpr double kInf = __builtin_huge_val();
-  static_assert(KB >= 2 && KB <= 16, "pool slots fit the key's low bits");
+  static_assert(KB >= 2 && KB <= 15, "pool slots fit the key's low bits (15 is an empty entry's)");
 
   __shared__ __align__(16) double s_row[kGroup * 16];  // W (9), o_g (3), D2c, sigma, -, -
   __shared__ uint4 s_win[kWindow];                     // (L,T) address (64 bits), row length, Gaussian index
@@ -231,12 +230,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
 
   // Pool: keys a[0 .. cnt) ascending, the rest kEmpty; the free payload slots
   // as a stack of 4-bit numbers.
-  using Stack = std::conditional_t<KB <= 8, uint32_t, uint64_t>;
   uint32_t a[KB];
 #pragma unroll
   for (int s = 0; s < KB; ++s) a[s] = kEmpty;
   uint32_t cnt = 0;
-  Stack free_slots = Stack(0xfedcba9876543210ull);
+  uint64_t free_slots = 0xfedcba9876543210ull;
   // The smallest dropped hit in (depth, index) order; every pooled hit is
   // before it.  Its depth and index are found from its list position when
   // first needed (e_tau: NaN until then).
@@ -719,10 +717,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void fo
 // resident waves.  8x8 tiles: 11 entries (ms at 1M / 100k Gaussians: 8: 1.00 /
 // 0.38, 9: 0.95 / 0.36, 10: 0.94 / 0.36, 11: 0.93 / 0.36, 12: 0.98 / 0.39; a
 // pool that overflows costs a rescan, 1640 of them at 8 entries and 13 at 11).
-// 16x16 tiles, whose list keys bound the depths more loosely: 12 (250k, ms:
-// 10: 0.66, 11: 0.76, 12: 0.54, 14: 0.59).  Deep frames (long tile lists, many
-// pending hits per ray): 15 (150k large Gaussians, ms: 14: 6.30, 15: 5.64,
-// 16, which leaves five waves per CU instead of six: 5.82).
+// 16x16 tiles, whose list keys bound the depths more loosely: 12 (us with 10,
+// 11, 12, 13, 14 entries at 250k Gaussians 979x546: 645, 576, 573, 559, 616; at
+// 100k 640x480: 418, 415, 410, 398, 420; at 1M 1237x822: 1185, 1134, 1160, 1136,
+// 1266).  Deep frames (long tile lists, many pending hits per ray): 15 (150k
+// large Gaussians, 8x8 tiles, ms: 13: 6.93, 14: 6.16, 15: 5.59; one more entry
+// leaves five waves per CU instead of six).  Where a frame becomes deep was
+// measured on 8x8 tiles; large Gaussians on 16x16 tiles gain from 15 entries
+// below it too (1024x680, ms with 12 and 15: 30k 3.93 and 3.84, 60k 8.6 and 5.5).
 constexpr int64_t kDeepListPairs = 2048;  // mean pairs per tile from which a frame counts as deep
 
 template <int TILE, int K, int KB>
