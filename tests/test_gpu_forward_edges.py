@@ -4,7 +4,9 @@ four, the chunks of 64 positions and the window of 128, copies of one Gaussian
 pending longer than the pool and the window hold.
 
 Against the fp64 oracle, at the bars of test_gpu_parity: pixels 1e-5 (fp32
-colours of order 1), hits per pixel exact, gradients 1e-4 relative L2.
+colours of order 1), hits per pixel exact, gradients 1e-4 relative L2.  Pixels
+within rounding of a decision are left out of all three: their upstream
+gradient is zero on both sides.
 """
 import numpy as np
 import pytest
@@ -22,14 +24,14 @@ def _check(sc, **kw):
     # (a margin of exactly 0 is a tie of equal depths, which the index decides on both sides)
     ok = (ren["margin"] >= 1e-9) | (ren["margin"] == 0)
     assert ok.mean() > 0.9
+    sc.dl_dimage.reshape(-1, 3)[~ok] = 0.0
     gpu = run_gpu(sc, **kw)
     assert np.array_equal(gpu["n_hits"][ok], ren["n_included"][ok])
     assert np.abs(gpu["image"].reshape(-1, 3) - ren["color"])[ok].max() <= 1e-5
     assert np.abs(gpu["t_final"].astype(np.float64) - ren["T_final"])[ok].max() <= 1e-6
-    if ok.all():
-        ref = o.backward(sc.dl_dimage)
-        for k, v in gpu["grads"].items():
-            assert rel_l2(v, ref[k]) <= 1e-4, k
+    ref = o.backward(sc.dl_dimage)
+    for k, v in gpu["grads"].items():
+        assert rel_l2(v, ref[k]) <= 1e-4, k
     return gpu
 
 
