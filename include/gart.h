@@ -216,8 +216,10 @@ typedef struct {
 
 enum {
   GART_CNT_FWD_HITS = 0,      /* composited hits written by the forward */
-  GART_CNT_FWD_TESTS = 1,     /* (pixel, Gaussian) ray tests in the forward */
-  GART_CNT_FWD_RESCANS = 2,   /* forward rescans of a tile list (hit-buffer overflow) */
+  GART_CNT_FWD_TESTS = 1,     /* (pixel, Gaussian) ray tests in the forward, those of a rescan that
+                                 starts before a pixel's own first dropped hit included */
+  GART_CNT_FWD_RESCANS = 2,   /* forward rescans of a tile list (hit-buffer overflow), per 8x8 block of
+                                 pixels: up to four per pass over the list of a 16x16 tile */
   GART_CNT_BWD_HITS = 3,      /* composited hits visited by the backward */
   GART_CNT_BWD_TESTS = 4,     /* (pixel, Gaussian) ray tests in the backward (scatter mode) */
   GART_CNT_BWD_ATOMICS = 5,   /* float atomic adds issued by the backward */

@@ -263,8 +263,8 @@ __global__ __launch_bounds__(kBoundsBlock) void bounds_kernel(BoundsArgs A) {
 }
 
 // One block adds up the blocks' partials (8-byte aligned, as the scratch may
-// be): latency-bound, so 1024 threads with four pairs each in flight (4 M Gaussians: 27 us with 256 threads and
-// single 8-byte loads).
+// be): latency-bound, so 1024 threads with four pairs each in flight (4 M
+// Gaussians: 8 us; 27 us with 256 threads and single 8-byte loads).
 constexpr int kTotalsThreads = 1024;
 __global__ __launch_bounds__(kTotalsThreads) void bounds_totals_kernel(const unsigned long long* __restrict__ part,
                                                                        int64_t nb,
@@ -410,9 +410,10 @@ __global__ __launch_bounds__(256) void emit_pairs_kernel(TileMapArgs A) {
     const double* Q = s_q[k];
     // The corner with the smallest N (c . u) / D and the one with the
     // largest s = |R^T u| / (c . u) are chosen by cross-multiplied
-    // comparisons (D > 0, and c . u > 0 where the result is used), so that one quotient (and one reciprocal
-    // root) per pair forms each value; a choice or a value off by rounding
-    // moves the bound by about 1e-15 relative, inside the 1e-12 margin below.
+    // comparisons (D > 0, and c . u > 0 where the result is used), so that one
+    // quotient (and one reciprocal root) per pair forms each value; a choice or
+    // a value off by rounding moves the bound by about 1e-15 relative, inside
+    // the 1e-12 margin below.
     // The refined estimates in place of correctly rounded operations: 98 to
     // 90 us for this kernel at 1 M Gaussians, 237 to 217 us at 4 M.
     double kn = 0.0, kd = 1.0, sw = 0.0, sc = 1.0;  // kmin = kn / kd, smax^2 = sw / sc^2

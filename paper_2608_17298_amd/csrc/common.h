@@ -17,9 +17,10 @@ namespace gart {
 
 constexpr int kGeomStride = 16;  // doubles per Gaussian in prim_geom
 // prim_geom layout (double): [0..8] W = S^-1 R^T row-major (times a power of
-// two for scales beyond 2^200), [9..11] o_g = W (o - mu), [12] squared clamp radius D2c, [13] opacity sigma, [14] lower
-// bound on the depth tau of any hit, [15] 1 - sigma = sigmoid(-logit)
-// (so that 1 - alpha keeps its precision for nearly opaque Gaussians).
+// two for scales beyond 2^200), [9..11] o_g = W (o - mu), [12] squared clamp
+// radius D2c, [13] opacity sigma, [14] lower bound on the depth tau of any hit,
+// [15] 1 - sigma = sigmoid(-logit) (so that 1 - alpha keeps its precision for
+// nearly opaque Gaussians).
 constexpr int kGeoW = 0, kGeoOg = 9, kGeoD2c = 12, kGeoSigma = 13, kGeoKey = 14, kGeoOneMinusSigma = 15;
 
 constexpr uint32_t kNoPrim = 0xffffffffu;

@@ -112,7 +112,7 @@ struct ForwardArgs {
   const int64_t* hl_off;    // [n_tiles+1] first hit_list row of each tile (tile^2 slots per row)
   uint32_t* tile_visit;     // [n_tiles][tile^2/64] one past the largest list position composited in each 8x8 block of the tile
   uint32_t* status;         // frame status word (GART_FRAME_* bits), cleared before the launch
-  int64_t pair_count;       // pairs in the tile lists (sizes the per-lane pending-hit rings)
+  int64_t pair_count;       // pairs in the tile lists (chooses the size of the per-lane pools of pending hits)
   uint64_t* counters;
   void* ev_begin;  // optional hipEvent_t recorded around the kernel
   void* ev_end;

@@ -264,9 +264,10 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
 // Small sorts in one launch: one block holds every pair (ITEMS per thread in
 // registers, exchanged through LDS between passes), with the same stable
 // ranking as radix_scatter_kernel.  Up to kSmallPairs: the device-wide passes
-// are bound there by their 16 launches (1000 pairs: 53 us, 4096: 57, 8192:
-// 63), while one CU's ranking grows with the pairs (13, 21 and 35 us) and with
-// 16 per thread would reach their time (16384: 66 us both).
+// are bound there by their 12 launches (three a pass: the 512 counts scan in
+// one; 1000 pairs: 53 us, 4096: 57, 8192: 63), while one CU's ranking grows
+// with the pairs (13, 21 and 35 us) and with 16 per thread would reach their
+// time (16384: 66 us both).
 // ---------------------------------------------------------------------------
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / 64;
